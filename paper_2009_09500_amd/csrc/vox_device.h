@@ -134,6 +134,33 @@ __host__ __device__ __forceinline__ void divmod_down(uint32_t x, uint32_t y, flo
     r = rr;
 }
 
+// ceil(x 2^23 / y) for x < y, 2 <= y <= 2^15, from the hardware reciprocal of
+// y (within one ulp): the float quotient is within three units, the integer
+// remainder to it is exact mod 2^32, and since remainders over y fall on
+// multiples of 2^-15, the bias of 2^-17 leaves their ceiling exact.
+__host__ __device__ __forceinline__ uint32_t fix23_ceil(uint32_t x, uint32_t y, float rcp) {
+    const uint32_t q = (uint32_t)((float)x * (rcp * 0x1p23f));
+    const int32_t rem = (int32_t)((x << 23) - mul_u24(q, y));
+    return q + (uint32_t)(int32_t)__builtin_ceilf((float)rem * rcp - 0x1p-17f);
+}
+
+// One minor axis of a piece in 23-bit fractions: eq. (3)'s quotient advances
+// at a step exactly when the fraction's sum passes one.  The fraction is the
+// remainder r over 2N at the piece's first voxel, the slope a / N, both
+// rounded up, so that after j steps the sum is less than j + 1 units too
+// large, and remainders are multiples of 1 / 2N: with j + 1 <= 256 and
+// 2N < 2^15 that is below the distance 2^23 / 2N of any fraction to the next
+// quotient, so every quotient is exact.  An axis as long as the dominant one
+// (two_a = two_n) advances at every step: 1 - 2^-23 a step from the middle.
+__host__ __device__ __forceinline__ uint32_t fix23_slope(uint32_t two_a, uint32_t two_n, float rcp) {
+    const uint32_t s = fix23_ceil(two_a < two_n ? two_a : 0u, two_n, rcp);
+    return two_a < two_n ? s : (1u << 23) - 1u;
+}
+__host__ __device__ __forceinline__ uint32_t fix23_fraction(uint32_t r, uint32_t two_a, uint32_t two_n, float rcp) {
+    const uint32_t f = fix23_ceil(r, two_n, rcp);
+    return two_a < two_n ? f : 1u << 22;
+}
+
 struct AxisStep {
     uint32_t q, r, two_a;
 };
