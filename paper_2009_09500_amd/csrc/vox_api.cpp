@@ -215,7 +215,7 @@ static vox_status segments_to_list(const vox_segment* d_segs, int64_t n, int64_t
             return device_fail(e, "count");
     } else {
         if ((e = vox::launch_list_count(segs, n, a8, w, s, kind)) != hipSuccess) return device_fail(e, "count");
-        if ((e = vox::launch_list_scan(w, n, d_offsets, cap, want, s)) != hipSuccess)
+        if ((e = vox::launch_list_scan(w, n, d_offsets, cap, s)) != hipSuccess)
             return device_fail(e, "scan");
         // (The Euclidean lists are written per segment: no output tiles.)
         if ((e = vox::launch_list_offsets(n, d_offsets, w, cap, want && !euclid, s)) != hipSuccess)

@@ -161,6 +161,26 @@ __host__ __device__ __forceinline__ uint32_t fix23_fraction(uint32_t r, uint32_t
     return two_a < two_n ? f : 1u << 22;
 }
 
+// int16 coordinates of eq. (3) in 16.16 fixed point, for N <= kFix16MaxN: the
+// high half of P + k d / N, P = p0 + 1/2, is the voxel's coordinate
+// p0 + floor((2 k d + N) / 2N) as long as the sum is never below its value and
+// less than 1 / 2N above it (values are multiples of 1 / 2N).  fix30_slope is
+// d / N in 2^-30, at most 1 + 2^-8 units too large; fix16_at the sum at any
+// k <= N, at most N (1 + 2^-8) 2^-14 + 1 < 1.24 units of 2^-16 too large; and
+// steps from there add fix16_step, at most 1.001 units too large each.  Seven
+// steps stay below 8.3 units, 2^16 / 2N is at least 8.4.
+constexpr uint32_t kFix16MaxN = 3900;
+__host__ __device__ __forceinline__ int32_t fix30_slope(int32_t d, double rcp_n) {
+    return (int32_t)__builtin_ceil((double)d * 0x1p30 * rcp_n + 0x1p-8);
+}
+__host__ __device__ __forceinline__ int32_t fix16_point(int32_t p0) {
+    return (int32_t)(((uint32_t)p0 << 16) + 0x8000u);
+}
+__host__ __device__ __forceinline__ int32_t fix16_at(int32_t point, int32_t slope, uint32_t k) {
+    return (int32_t)((uint32_t)point + (uint32_t)(((int64_t)(int32_t)k * slope + 16383) >> 14));
+}
+__host__ __device__ __forceinline__ int32_t fix16_step(int32_t slope) { return (slope + 16383) >> 14; }
+
 struct AxisStep {
     uint32_t q, r, two_a;
 };
