@@ -41,32 +41,65 @@ __device__ __forceinline__ uint32_t list_euclid_length(const Seg& s) {
 // Samples of [k0, k1) (k0 < k1 <= N + 1, N >= 1) of an int16-range
 // segment that start a new voxel under the Euclidean N: sample k0 from its
 // remainders (one division unless k0 = 0), then one step a sample.
+//
+// Up to N = 32767 an axis is a 32-bit fraction f and a slope d, and moves at a
+// step exactly when f + d carries: the remainder over 2N and a / N in 2^-32,
+// each rounded up by less than 1.2 units, so that after all N steps the sum is
+// less than 1.2 (N + 2) < 2^32 / 2N units too large.  A step is three adds with
+// carry and one add of the (or-ed) carries.  An axis with a = N moves at every
+// step, and then so does the sample.  Longer segments step their remainders.
 template <bool kFromStart>
 __device__ __forceinline__ uint32_t euclid_walk(const Seg& g, uint32_t N, uint32_t k0, uint32_t k1) {
     const uint32_t two_n = 2u * N;
-    uint32_t ta[3], f[3];
-    bool moved = k0 == 0u;
+    uint32_t ta[3], r[3];
+    bool moved = k0 == 0u, tie = false;
     const float rcpd = rcp_down(two_n);
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         const int32_t d = g.p1[ax] - g.p0[ax];
         const uint32_t neg = d < 0 ? 1u : 0u;
         ta[ax] = 2u * (uint32_t)(d < 0 ? -d : d);
-        uint32_t r;
+        tie |= ta[ax] == two_n;
         if (kFromStart || k0 == 0u) {
-            r = N - neg;
+            r[ax] = N - neg;
         } else if (N <= 32767u) {
             // 2 k0 a + N < 2^31, 2N < 2^16, quotient <= a < 2^15.
             uint32_t q;
-            divmod_down(2u * k0 * (ta[ax] >> 1) + N - neg, two_n, rcpd, q, r);
+            divmod_down(2u * k0 * (ta[ax] >> 1) + N - neg, two_n, rcpd, q, r[ax]);
         } else {
-            r = (uint32_t)(((uint64_t)k0 * ta[ax] + N - neg) % two_n);
+            r[ax] = (uint32_t)(((uint64_t)k0 * ta[ax] + N - neg) % two_n);
         }
-        moved |= r < ta[ax];
-        f[ax] = r - two_n;
+        moved |= r[ax] < ta[ax];
     }
     uint32_t c = moved ? 1u : 0u;
-    for (uint32_t k = k0 + 1u; k < k1; ++k) {
+    const uint32_t steps = k1 - k0 - 1u;
+    if (tie) return c + steps;
+    if (N <= 32767u) {
+        const double unit = 0x1p32 / (double)two_n;
+        uint32_t f[3], d[3];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            f[ax] = (uint32_t)__builtin_ceil((double)r[ax] * unit + 0.125);
+            d[ax] = (uint32_t)__builtin_ceil((double)ta[ax] * unit + 0.125);
+        }
+        auto step = [&] {
+            const bool a = __builtin_uadd_overflow(f[0], d[0], &f[0]);
+            const bool b = __builtin_uadd_overflow(f[1], d[1], &f[1]);
+            const bool e = __builtin_uadd_overflow(f[2], d[2], &f[2]);
+            c += (a | b | e) ? 1u : 0u;
+        };
+        uint32_t k = 0;
+        for (; k + 8u <= steps; k += 8u) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) step();
+        }
+        for (; k < steps; ++k) step();
+        return c;
+    }
+    uint32_t f[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) f[ax] = r[ax] - two_n;
+    for (uint32_t k = 0; k < steps; ++k) {
         bool mv = false;
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
@@ -120,8 +153,13 @@ __global__ __launch_bounds__(kCountBlock) void k_euclid_counts(const int32_t* __
     }
 }
 
-// Flag of the header's second word: some segment is longer than kFix16MaxN.
+// Flag of the header's second word: some segment is too long for the 16.16
+// coordinates of the int16 lists.
 constexpr int32_t kListLong = 4;
+template <int kKind>
+__device__ __forceinline__ bool list_long(const Seg& g) {
+    return kKind == kListI16 && seg_length(g) > (int64_t)kFix16MaxN;
+}
 
 // Bitwise OR over the block.
 template <int kBlock>
@@ -179,7 +217,7 @@ __global__ __launch_bounds__(kCountBlock) void k_list_count(const int32_t* __res
             } else {
                 c = seg_length(g) + 1;
             }
-            flag |= (inr ? 0 : kStatusOutOfRange) | (c - 1 > (int64_t)kFix16MaxN ? kListLong : 0);
+            flag |= (inr ? 0 : kStatusOutOfRange) | (list_long<kKind>(g) ? kListLong : 0);
             // Counts above 2^32 - 1 only arise from out-of-range input.
             counts[i] = c > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)c;
             sum += c > 0xFFFFFFFFll ? 0xFFFFFFFFll : c;
@@ -324,7 +362,7 @@ __global__ __launch_bounds__(kCountBlock) void k_list_one_block(
             } else {
                 v = seg_length(g) + 1;
             }
-            flag |= (inr ? 0 : kStatusOutOfRange) | (v - 1 > (int64_t)kFix16MaxN ? kListLong : 0);
+            flag |= (inr ? 0 : kStatusOutOfRange) | (list_long<kKind>(g) ? kListLong : 0);
             c[s] = v > 0xFFFFFFFFll ? 0xFFFFFFFFll : v;
             counts[i] = (uint32_t)c[s];
         }
@@ -709,7 +747,6 @@ void k_list_voxels(
 // 32 bits exactly when r + dr >= 2N).  A sample k >= 1 starts a new voxel
 // when some axis moved from k - 1 to k, that is when r_a(k) < 2a_a for some
 // a, i.e. f_a < 2a_a - 2N as signed values (|2N| < 2^31).
-template <int kLanes>
 struct ListSamples {
     uint32_t c[3], f[3], h[3], dq[3], dr[3], mk[3];
     uint32_t N, two_n;
@@ -736,7 +773,7 @@ struct ListSamples {
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 divmod_down(__umul24(k, two_a[ax]) + num0[ax], two_n, rcpd, q[ax], r[ax]);
-                divmod_down(kLanes * two_a[ax], two_n, rcpd, dq[ax], dr[ax]);
+                divmod_down(kWave * two_a[ax], two_n, rcpd, dq[ax], dr[ax]);
             }
         } else {
 #pragma unroll
@@ -744,7 +781,7 @@ struct ListSamples {
                 const uint64_t num = (uint64_t)k * two_a[ax] + num0[ax];
                 q[ax] = (uint32_t)(num / two_n);
                 r[ax] = (uint32_t)(num - (uint64_t)q[ax] * two_n);
-                const uint32_t s = kLanes * two_a[ax];
+                const uint32_t s = kWave * two_a[ax];
                 dq[ax] = s / two_n;
                 dr[ax] = s - dq[ax] * two_n;
             }
@@ -776,46 +813,295 @@ struct ListSamples {
     __device__ __forceinline__ int32_t coord(int ax) const { return (int32_t)(c[ax] ^ mk[ax]); }
 };
 
-// Lists with the Euclidean N of eq. (1).  A wave takes 64 / kLanes segments,
-// kLanes lanes each; a segment's lanes take its samples k = 0..N kLanes at a
-// time, each stepping its own samples and deciding alone whether its sample
-// starts a new voxel (ListSamples); a ballot of those decisions places the
-// kept voxels, and consecutive lanes write consecutive voxels.
-template <bool kAligned8, int kLanes>
-__global__ __launch_bounds__(kCountBlock) void k_list_voxels_euclid(
-    const int32_t* __restrict__ segs, int64_t n, const int64_t* __restrict__ offsets,
-    int16_t* __restrict__ voxels, const int32_t* __restrict__ status) {
-    if (*status != 0) return;
-    static_assert(kLanes >= 2 && kLanes <= kWave && (kWave % kLanes) == 0, "lanes a segment");
-    constexpr int kSlots = kWave / kLanes;
-    const uint32_t lane = threadIdx.x % kWave;
-    const uint32_t sub = lane % kLanes;
-    const uint32_t slot = lane / kLanes;
-    const uint64_t slot_bits = (kLanes == kWave ? ~0ull : ((1ull << kLanes) - 1)) << (kLanes * slot);
-    const int64_t step = (int64_t)gridDim.x * (kCountBlock / kWave) * kSlots;
-    for (int64_t i0 = ((int64_t)blockIdx.x * (kCountBlock / kWave) + threadIdx.x / kWave) * kSlots; i0 < n;
-         i0 += step) {
-        const int64_t i = i0 + slot;
-        const bool valid = i < n;
-        Seg g = {};
-        if (valid) g = load_seg<kAligned8>(segs, i);
-        ListSamples<kLanes> s;
-        bool moved = s.start(g, list_euclid_length(g), sub);
-        int16_t* out = voxels + 3 * (valid ? offsets[i] : 0);
-        for (uint32_t c0 = 0; __ballot(valid && c0 <= s.N) != 0; c0 += kLanes) {
-            if (c0 != 0) moved = s.next();
-            const bool keep = moved && valid && c0 + sub <= s.N;
-            const uint64_t m = __ballot(keep) & slot_bits;
-            if (keep) {
-                const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                int16_t* o = out + 3 * before;
+// The Euclidean voxels of a segment of any int16 length, by a wave: the lanes
+// take its samples 64 at a time, each stepping its own samples and deciding
+// alone whether its sample starts a new voxel (ListSamples); a ballot of those
+// decisions places the kept voxels, and consecutive lanes write consecutive
+// voxels.  Returns their number.
+__device__ __forceinline__ uint32_t euclid_voxels_any(const Seg& g, int16_t* out) {
+    const uint32_t lane = __lane_id();
+    ListSamples s;
+    bool moved = s.start(g, list_euclid_length(g), lane);
+    uint32_t rows = 0;
+    for (uint32_t c0 = 0; c0 <= s.N; c0 += kWave) {
+        if (c0 != 0) moved = s.next();
+        const bool keep = moved && c0 + lane <= s.N;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        if (keep) {
+            const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            int16_t* o = out + 3 * (uint64_t)(rows + before);
 #pragma unroll
-                for (int ax = 0; ax < 3; ++ax) o[ax] = (int16_t)s.coord(ax);
+            for (int ax = 0; ax < 3; ++ax) o[ax] = (int16_t)s.coord(ax);
+        }
+        rows += (uint32_t)__popcll(m);
+    }
+    return rows;
+}
+
+// Lists with the Euclidean N of eq. (1).  A wave takes up to 64 consecutive
+// segments: a lane each for what depends on the segment alone (LDS), then kL
+// lanes each for the samples, a run of up to kEuclidRun consecutive ones a
+// lane; kL is the least that gives all but four of the wave's segments one run
+// a lane, and a longer segment takes all lanes, window by window.  Per axis the
+// coordinate at sample k is the high word of start + k slope (64 bits), the
+// fraction its low word, and a step's carry out of the fraction is a move of
+// the axis, so the kept samples of a run are counted with three adds a sample,
+// and after a scan of the counts over the lanes a second walk puts them in
+// place: six adds, the packing of a row and two LDS writes a sample.  (Lanes
+// stepping strided samples and a ballot for every 64 took 28 instructions a
+// sample, and 0.196 ms for 1 M segments of 64 samples; this one 0.131 ms, and
+// 0.177 against 0.323 ms for 11 M segments of 5 samples.)
+//
+// Exact: start and slope are rounded up by less than 1.2 units of 2^-32, so at
+// sample k the sum is less than 1.2 (N + 1) <= 2^32 / 2N units too large, and
+// its values are multiples of 1 / 2N.  An axis with a = N, which moves at every
+// step, takes the slope 1 - 2^-32 from a start of 1/2.
+//
+// The wave's output is contiguous: rows go through an LDS buffer, x and y apart
+// from z (rows of 6 bytes would take unaligned writes, five times as slow), and
+// from there to memory, two rows a lane, in whole 128-byte lines past the caches
+// (0.147 ms a call of 1 M segments of 64-110 samples, against 0.157 through
+// them; lines written in parts past them 0.182).  What bounds it: about 350
+// instructions a group of 64 lanes, 60 % of the issue slots, and their latency.
+// Runs of 7 / 9 / 11 / 15 (less LDS, more waves, against fewer set-ups a sample):
+// 0.139 / 0.144 / 0.156 / 0.148 ms, but 0.161 / 0.126 / 0.125 / 0.150 for the
+// kernel on 400 000 segments of 171 samples.
+constexpr uint32_t kEuclidMaxN = 32767;
+constexpr uint32_t kEuclidRun = 9;                        // samples of a lane at a time
+constexpr uint32_t kEuclidBuffer = kWave * kEuclidRun;    // rows
+constexpr uint32_t kEuclidGroup = 64;                     // rows of whole 128-byte lines of memory: 3 x 128 / 6
+struct EuclidSeg {
+    uint32_t c[3];      // p0 ^ m, m the sign mask of d (c' = c ^ m grows by one on every move)
+    uint32_t slope[3];  // a / N
+    uint32_t n_neg;     // N | sign bits of d << 24
+    uint32_t start;     // 2^-32 / 2N units of the start of a negative axis: 1/2 - 1/2N
+};
+struct EuclidWave {
+    EuclidSeg seg[kWave];
+    __align__(16) uint32_t xy[kEuclidBuffer + kEuclidGroup];
+    __align__(16) uint16_t z[kEuclidBuffer + kEuclidGroup];
+};
+
+template <bool kAligned8>
+struct EuclidLists {
+    EuclidWave& w;
+    int16_t* voxels;
+    int64_t base;       // the wave's first voxel
+    uint32_t from = 0, to = 0;  // voxels in the buffer, relative to base
+
+    static __device__ __forceinline__ void fence() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+
+    // Place in the buffer of voxel base + v: groups of places are groups of
+    // the list's rows.
+    __device__ __forceinline__ uint32_t place(uint32_t v) const {
+        return ((uint32_t)(base + from) % kEuclidGroup) + (v - from);
+    }
+
+    // Writes the buffer's whole groups of rows, or all rows.
+    __device__ __forceinline__ void flush(bool all) {
+        const uint32_t h0 = place(from), h2 = place(to), h1 = all ? h2 : h2 / kEuclidGroup * kEuclidGroup;
+        if (h1 <= h0) return;
+        fence();
+        const uint32_t lane = __lane_id();
+        int16_t* dst = voxels + 3 * (base + from - h0);
+        // Four units a lane in flight.
+        constexpr uint32_t kUnits = 4;
+        for (uint32_t u0 = (h0 + 1u) / 2u + lane; u0 < h1 / 2u; u0 += kWave * kUnits) {
+            uint2 p[kUnits];
+            uint32_t q[kUnits];
+#pragma unroll
+            for (uint32_t i = 0; i < kUnits; ++i) {
+                const uint32_t u = u0 + i * kWave < (kEuclidBuffer + kEuclidGroup) / 2u ? u0 + i * kWave : 0u;
+                p[i] = reinterpret_cast<const uint2*>(w.xy)[u];
+                q[i] = reinterpret_cast<const uint32_t*>(w.z)[u];
             }
-            out += 3 * __popcll(m);
+#pragma unroll
+            for (uint32_t i = 0; i < kUnits; ++i) {
+                const uint32_t u = u0 + i * kWave;
+                if (u < h1 / 2u) {
+                    uint32_t* row2 = reinterpret_cast<uint32_t*>(dst) + 3u * u;
+                    __builtin_nontemporal_store(p[i].x, row2);
+                    __builtin_nontemporal_store((q[i] & 0xFFFFu) | (p[i].y << 16), row2 + 1);
+                    __builtin_nontemporal_store((p[i].y >> 16) | (q[i] & 0xFFFF0000u), row2 + 2);
+                }
+            }
+        }
+        // A row whose pair is not here, first or last.
+        const uint32_t odd = lane == 0 ? h0 : h1 - 1u;
+        if ((lane == 0 && (h0 & 1u) != 0u) || (lane == 1 && (h1 & 1u) != 0u)) {
+            dst[3 * odd] = (int16_t)w.xy[odd];
+            dst[3 * odd + 1] = (int16_t)(w.xy[odd] >> 16);
+            dst[3 * odd + 2] = (int16_t)w.z[odd];
+        }
+        // The rows of the group begun move to its place at the front.
+        const uint32_t left = h1 + lane < h2 ? h1 + lane : h0;
+        const uint32_t xy = w.xy[left];
+        const uint16_t z = w.z[left];
+        fence();
+        if (h1 + lane < h2) {
+            w.xy[lane] = xy;
+            w.z[lane] = z;
+        }
+        fence();
+        from += h1 - h0;
+    }
+
+    // Samples [win, win + kL kEuclidRun) of segments [s0, s0 + 64 / kL) of the
+    // wave's (below cnt), whose rows follow the buffer's last one; returns the
+    // number of rows.
+    template <int kL>
+    __device__ __forceinline__ uint32_t run(uint32_t s0, uint32_t cnt, uint32_t win, uint32_t at) {
+        const uint32_t lane = __lane_id(), sub = lane % kL, slot = lane / kL;
+        const bool valid = s0 + slot < cnt;
+        const EuclidSeg e = w.seg[valid ? s0 + slot : s0];
+        const uint32_t N = e.n_neg & 0xFFFFFFu;
+        // This lane's samples [k0, k0 + len).
+        const uint32_t left = N + 1u - win, share = left < kL * kEuclidRun ? (left + kL - 1u) / kL : kEuclidRun;
+        const uint32_t k0 = win + sub * share;
+        const uint32_t len = !valid || k0 > N ? 0u : (N + 1u - k0 < share ? N + 1u - k0 : share);
+        uint32_t c[3], f[3], g[3], mk[3];
+        bool kept = k0 == 0u;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const bool neg = ((e.n_neg >> (24 + a)) & 1u) != 0u;
+            mk[a] = neg ? ~0u : 0u;
+            const uint64_t t = (uint64_t)k0 * e.slope[a] +
+                               (neg && e.slope[a] != ~0u ? e.start : 0x80000000u);
+            c[a] = e.c[a] + (uint32_t)(t >> 32);
+            f[a] = g[a] = (uint32_t)t;
+            kept |= f[a] < e.slope[a];  // the step to k0 carried
+        }
+        kept &= len != 0u;
+        uint32_t rows = kept ? 1u : 0u;
+        for (uint32_t j = 1; j < len; ++j) {
+            const bool x = __builtin_uadd_overflow(g[0], e.slope[0], &g[0]);
+            const bool y = __builtin_uadd_overflow(g[1], e.slope[1], &g[1]);
+            const bool z = __builtin_uadd_overflow(g[2], e.slope[2], &g[2]);
+            rows += (x | y | z) ? 1u : 0u;
+        }
+        const uint32_t incl = wave_inclusive_sum_dpp(rows);
+        uint32_t o = at + (incl - rows);
+        const uint32_t mxy = (mk[0] & 0xFFFFu) | (mk[1] << 16);
+        auto put = [&] {
+            w.xy[o] = __builtin_amdgcn_perm(c[1], c[0], 0x05040100u) ^ mxy;
+            w.z[o] = (uint16_t)(c[2] ^ mk[2]);
+            ++o;
+        };
+        if (kept) put();
+        for (uint32_t j = 1; j < len; ++j) {
+            const bool x = __builtin_uadd_overflow(f[0], e.slope[0], &f[0]);
+            const bool y = __builtin_uadd_overflow(f[1], e.slope[1], &f[1]);
+            const bool z = __builtin_uadd_overflow(f[2], e.slope[2], &f[2]);
+            c[0] += x ? 1u : 0u;
+            c[1] += y ? 1u : 0u;
+            c[2] += z ? 1u : 0u;
+            if (x | y | z) put();
+        }
+        return __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+
+    // Segment t of the wave's, of length n, with all lanes.
+    __device__ __forceinline__ void one(const int32_t* __restrict__ segs, int64_t i0, uint32_t t, uint32_t n) {
+        if (n > kEuclidMaxN) {
+            flush(true);
+            to += euclid_voxels_any(load_seg<kAligned8>(segs, i0 + t), voxels + 3 * (base + to));
+            from = to;
+        } else {
+            for (uint32_t win = 0; win <= n; win += kWave * kEuclidRun) {
+                to += run<kWave>(t, t + 1u, win, place(to));
+                flush(false);
+            }
         }
     }
+
+    // The wave's cnt segments, kL lanes each; lane t holds the N of segment t.
+    template <int kL>
+    __device__ __forceinline__ void groups(const int32_t* __restrict__ segs, int64_t i0, uint32_t cnt, uint32_t N) {
+        constexpr uint32_t kSlots = kWave / kL;
+        const uint64_t longer = __builtin_amdgcn_ballot_w64((uint32_t)__lane_id() < cnt && N >= kL * kEuclidRun);
+        for (uint32_t s = 0; s < cnt; s += kSlots) {
+            if (kL < kWave && ((longer >> s) & (~0ull >> (kWave - kSlots))) == 0) {
+                to += run<kL>(s, cnt, 0u, place(to));
+                flush(false);
+            } else {
+                for (uint32_t t = s; t < cnt && t < s + kSlots; ++t) one(segs, i0, t, __builtin_amdgcn_readlane(N, t));
+            }
+        }
+    }
+
+    // Segments [i0, i0 + cnt), cnt <= 64.
+    __device__ __forceinline__ void wave(const int32_t* __restrict__ segs, const int64_t* __restrict__ offsets,
+                                         int64_t i0, uint32_t cnt) {
+        const uint32_t lane = __lane_id();
+        const int64_t i = i0 + (lane < cnt ? lane : cnt - 1u);
+        const Seg g = load_seg<kAligned8>(segs, i);
+        const int64_t o = offsets[i0];
+        base = ((int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(o >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)o);
+        from = to = 0u;
+        const uint32_t N = list_euclid_length(g);
+        const double rcp_n = N ? 1.0 / (double)N : 0.0;
+        EuclidSeg e;
+        e.n_neg = N;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int32_t d = g.p1[a] - g.p0[a];
+            const uint32_t len = (uint32_t)(d < 0 ? -d : d);
+            e.c[a] = (uint32_t)g.p0[a] ^ (d < 0 ? ~0u : 0u);
+            e.slope[a] = len == N ? ~0u : (uint32_t)__builtin_ceil((double)len * 0x1p32 * rcp_n + 0.125);
+            e.n_neg |= d < 0 ? 1u << (24 + a) : 0u;
+        }
+        e.start = 0x80000000u - (uint32_t)(0x1p31 * rcp_n);
+        w.seg[lane] = e;
+        fence();
+        // Lanes a segment: all but a few of the wave's segments in one pass.
+        uint32_t lanes = 1;
+        while (lanes < (uint32_t)kWave &&
+               (lanes * cnt <= kWave / 2u ||
+                __popcll(__builtin_amdgcn_ballot_w64(lane < cnt && N >= lanes * kEuclidRun)) > 4))
+            lanes *= 2u;
+        switch (lanes) {
+            case 1: groups<1>(segs, i0, cnt, N); break;
+            case 2: groups<2>(segs, i0, cnt, N); break;
+            case 4: groups<4>(segs, i0, cnt, N); break;
+            case 8: groups<8>(segs, i0, cnt, N); break;
+            case 16: groups<16>(segs, i0, cnt, N); break;
+            case 32: groups<32>(segs, i0, cnt, N); break;
+            default: groups<64>(segs, i0, cnt, N); break;
+        }
+        flush(true);
+        fence();  // the segments are rewritten by the wave's next ones
+    }
+};
+
+template <bool kAligned8>
+__global__ __launch_bounds__(kCountBlock) void k_list_voxels_euclid(
+    const int32_t* __restrict__ segs, int64_t n, const int64_t* __restrict__ offsets,
+    int16_t* __restrict__ voxels, const int32_t* __restrict__ status, int32_t per_wave) {
+    __shared__ EuclidWave waves[kCountBlock / kWave];
+    if (status[0] != 0) return;
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    EuclidLists<kAligned8> lists{waves[wv], voxels, 0};
+    constexpr int kWaves = kCountBlock / kWave;
+    const int64_t step = (int64_t)gridDim.x * kWaves * per_wave;
+    for (int64_t i0 = ((int64_t)blockIdx.x * kWaves + wv) * per_wave; i0 < n; i0 += step)
+        lists.wave(segs, offsets, i0, n - i0 < per_wave ? (uint32_t)(n - i0) : (uint32_t)per_wave);
+}
+
+template <bool kAligned8>
+__global__ __launch_bounds__(kCountBlock) void k_list_voxels_euclid_any(
+    const int32_t* __restrict__ segs, int64_t n, const int64_t* __restrict__ offsets,
+    int16_t* __restrict__ voxels, const int32_t* __restrict__ status) {
+    if (status[0] != 0) return;
+    constexpr int kWaves = kCountBlock / kWave;
+    const int64_t step = (int64_t)gridDim.x * kWaves;
+    for (int64_t i = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave; i < n; i += step)
+        euclid_voxels_any(load_seg<kAligned8>(segs, i), voxels + 3 * offsets[i]);
 }
 
 // ---------------------------------------------------------------- host side
@@ -889,15 +1175,9 @@ static void launch_euclid_counts(const int32_t* segs, int64_t n, bool aligned8, 
 
 template <int kKind>
 static void list_count(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w, hipStream_t stream) {
-    // One lane a segment and short segments (at most 32 voxels on average by
-    // the capacity, or none given): the count kernel walks the segments
-    // itself, one launch fewer (1 M segments of 9-14 samples 0.018 -> 0.014
-    // ms).  Longer ones keep k_euclid_counts, a thread per segment rather
-    // than per four (1 M segments of 64-110 samples: 0.041 against 0.044 ms).
-    const int walk = kKind == kListEuclid && n > 0 && euclid_count_lanes(n, w) == 1 &&
-                             w.ntiles * kListTile / n <= 32
-                         ? 1
-                         : 0;
+    // With one lane a segment the count kernel walks the segments itself, one
+    // launch fewer (1 M segments of 64 samples: 0.031 against 0.046 ms).
+    const int walk = kKind == kListEuclid && n > 0 && euclid_count_lanes(n, w) == 1 ? 1 : 0;
     if (kKind == kListEuclid && n > 0 && !walk) launch_euclid_counts(segs, n, aligned8, w, stream);
     // n == 0: one block that writes a zero sum and no flag.
     dim3 grid(n == 0 ? 1u : (unsigned)w.nb);
@@ -1018,44 +1298,49 @@ hipError_t launch_list_voxels32(const int32_t* segs, int64_t n, bool aligned8, c
     return hipGetLastError();
 }
 
-template <int kLanes>
+// Segments of a wave: 64 share one preparation, but few long ones spread over
+// the chip.
 static void list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
                                const ListWork& w, int16_t* voxels, hipStream_t stream) {
-    constexpr int kSegsPerBlock = kCountBlock / kLanes;
-    int64_t blocks = (n + kSegsPerBlock - 1) / kSegsPerBlock;
+    int64_t per = n / 8192;
+    per = per < 1 ? 1 : (per > kWave ? kWave : per);
+    const int64_t segs_per_block = per * (kCountBlock / kWave);
+    int64_t blocks = (n + segs_per_block - 1) / segs_per_block;
     if (blocks > 16384) blocks = 16384;
     if (aligned8)
-        k_list_voxels_euclid<true, kLanes><<<dim3((unsigned)blocks), kCountBlock, 0, stream>>>(segs, n, offsets,
-                                                                                               voxels, w.status);
+        k_list_voxels_euclid<true><<<dim3((unsigned)blocks), kCountBlock, 0, stream>>>(
+            segs, n, offsets, voxels, w.status, (int32_t)per);
     else
-        k_list_voxels_euclid<false, kLanes><<<dim3((unsigned)blocks), kCountBlock, 0, stream>>>(segs, n, offsets,
-                                                                                                voxels, w.status);
+        k_list_voxels_euclid<false><<<dim3((unsigned)blocks), kCountBlock, 0, stream>>>(
+            segs, n, offsets, voxels, w.status, (int32_t)per);
 }
 
-// Lanes a segment for the Euclidean list kernel: about one pass of the
-// lanes per segment (at least 4 lanes, a pass covering up to 8 voxels a
-// lane), and at least 65 536 lanes in all so that a few long segments still
-// spread over the chip.  The voxels per segment are taken from the caller's
-// capacity (the workspace's tile count), so an oversized buffer only costs
-// speed.
-static int euclid_list_lanes(int64_t n, int64_t capacity) {
-    const int64_t avg = capacity / n;
-    int lanes = 4;
-    while (lanes < kWave && ((int64_t)lanes * 8 < avg || n * lanes < 65536)) lanes *= 2;
-    return lanes;
+// Segments of more voxels than this on average (by the caller's capacity) take
+// the general form with a wave each: its stores are whole rounds of 64 samples
+// and it needs no LDS, hence twice the waves.  68 M voxels in segments of 500 /
+// 1000 / 2000 samples: 0.130 / 0.118 / 0.107 ms against 0.127 / 0.126 / 0.127.
+constexpr int64_t kEuclidAnyVoxels = 750;
+
+static void list_voxels_euclid_any(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
+                                   const ListWork& w, int16_t* voxels, hipStream_t stream) {
+    int64_t blocks = (n + kCountBlock / kWave - 1) / (kCountBlock / kWave);
+    if (blocks > 16384) blocks = 16384;
+    if (aligned8)
+        k_list_voxels_euclid_any<true><<<dim3((unsigned)blocks), kCountBlock, 0, stream>>>(segs, n, offsets,
+                                                                                           voxels, w.status);
+    else
+        k_list_voxels_euclid_any<false><<<dim3((unsigned)blocks), kCountBlock, 0, stream>>>(segs, n, offsets,
+                                                                                            voxels, w.status);
 }
 
 hipError_t launch_list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
                                      const ListWork& w, int16_t* voxels, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     KernelTimer timer("list_voxels_euclid", stream);
-    switch (euclid_list_lanes(n, w.ntiles * kListTile)) {
-        case 4: list_voxels_euclid<4>(segs, n, aligned8, offsets, w, voxels, stream); break;
-        case 8: list_voxels_euclid<8>(segs, n, aligned8, offsets, w, voxels, stream); break;
-        case 16: list_voxels_euclid<16>(segs, n, aligned8, offsets, w, voxels, stream); break;
-        case 32: list_voxels_euclid<32>(segs, n, aligned8, offsets, w, voxels, stream); break;
-        default: list_voxels_euclid<64>(segs, n, aligned8, offsets, w, voxels, stream); break;
-    }
+    if (w.ntiles * kListTile / n > kEuclidAnyVoxels)
+        list_voxels_euclid_any(segs, n, aligned8, offsets, w, voxels, stream);
+    else
+        list_voxels_euclid(segs, n, aligned8, offsets, w, voxels, stream);
     return hipGetLastError();
 }
 

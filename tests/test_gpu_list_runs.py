@@ -1,12 +1,18 @@
 """The voxel lists at the edges of their inner forms, voxel by voxel against the
-oracle: the longest segments of the fixed-point forms and one more."""
+oracle: the longest segments of the fixed-point forms and one more, and for the
+Euclidean lists every number of lanes a segment with segments of one run a lane
+and one sample more, few long segments, and segments of every kind in turn."""
 
 import numpy as np
 import pytest
 
+from tests.test_gpu_euclid import assert_list
 from tests.test_gpu_list import assert_parity
 
 pytestmark = pytest.mark.gpu
+
+RUN = 9  # samples of a lane at a time
+
 
 def axis_aligned_mix(rng, lengths):
     """Segments of these axis lengths: a third along an axis, the rest with two
@@ -29,3 +35,31 @@ def test_list_fixed_point_bound(longest, n):
     lengths = rng.integers(0, 60, n)
     lengths[rng.integers(0, n, 3)] = longest
     assert_parity(axis_aligned_mix(rng, lengths))
+
+
+@pytest.mark.parametrize("longest", [18900, 32767, 32768, 40000])
+def test_euclid_fixed_point_bound(longest):
+    rng = np.random.default_rng(longest)
+    lengths = rng.integers(0, 400, 700)
+    lengths[::100] = longest
+    assert_list(axis_aligned_mix(rng, lengths))
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 8, 16, 32, 64])
+def test_euclid_lanes(lanes):
+    rng = np.random.default_rng(lanes)
+    n = 65536 // lanes + 1
+    lengths = rng.integers(0, RUN * lanes + 2, n)
+    lengths[: n // 2] = np.minimum(lengths[: n // 2], RUN * lanes * 4 // 7)
+    lengths[1] = RUN * lanes - 1
+    lengths[2] = RUN * lanes
+    lengths[n // 2 :: 97] = 0
+    lengths[n // 2] = 3 * 64 * RUN + 1
+    lengths[n - 1] = 40000 if lanes in (1, 8) else 64 * RUN
+    assert_list(axis_aligned_mix(rng, lengths))
+
+
+@pytest.mark.parametrize("n", [1, 3, 600])
+def test_euclid_long_segments(n):
+    rng = np.random.default_rng(n)
+    assert_list(axis_aligned_mix(rng, rng.integers(1200, 2000, n)))
