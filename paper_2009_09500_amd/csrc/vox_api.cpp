@@ -209,9 +209,14 @@ static vox_status segments_to_list(const vox_segment* d_segs, int64_t n, int64_t
     const bool a8 = aligned(d_segs, 8);
     vox::ListWork w = vox::list_workspace(d_work, n, cap);
     hipError_t e;
-    if (n >= 1 && n <= vox::kSegsPerCountBlock) {
+    const bool at_once = want && !euclid && vox::list_one_launch(n, cap);
+    if (at_once) {
+        // (The kernel itself checks the header before it writes a voxel.)
+        if ((e = vox::launch_list_all(segs, n, a8, d_offsets, w, d_voxels, cap, s, kind)) != hipSuccess)
+            return device_fail(e, "voxels");
+    } else if (n >= 1 && n <= vox::kSegsPerCountBlock) {
         // One block counts, scans and places.
-        if ((e = vox::launch_list_one_block(segs, n, a8, w, d_offsets, cap, want, s, kind)) != hipSuccess)
+        if ((e = vox::launch_list_one_block(segs, n, a8, w, d_offsets, cap, s, kind)) != hipSuccess)
             return device_fail(e, "count");
     } else {
         if ((e = vox::launch_list_count(segs, n, a8, w, s, kind)) != hipSuccess) return device_fail(e, "count");
@@ -246,14 +251,13 @@ static vox_status segments_to_list(const vox_segment* d_segs, int64_t n, int64_t
             tiles = want ? (hdr[1] + vox::kListTile - 1) / vox::kListTile : 0;
         }
     }
-    if (tiles > 0) {
+    if (tiles > 0 && !at_once) {
         if (euclid)
             e = vox::launch_list_voxels_euclid(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), s);
         else if (kind == vox::kListI32)
             e = vox::launch_list_voxels32(segs, n, a8, d_offsets, w, static_cast<int32_t*>(d_voxels), tiles, s);
         else
-            e = vox::launch_list_voxels(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), cap, tiles,
-                                        s);
+            e = vox::launch_list_voxels(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), tiles, s);
         if (e != hipSuccess) return device_fail(e, "voxels");
     }
     return result == VOX_OK ? ok() : result;

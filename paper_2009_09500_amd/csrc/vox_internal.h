@@ -71,16 +71,20 @@ hipError_t launch_list_count(const int32_t* segs, int64_t n, bool aligned8, cons
                              hipStream_t stream, ListKind kind);
 // Count, scan and offsets in one block, for 1 <= n <= kSegsPerCountBlock.
 hipError_t launch_list_one_block(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w,
-                                 int64_t* offsets, int64_t capacity, bool want_voxels, hipStream_t stream,
+                                 int64_t* offsets, int64_t capacity, hipStream_t stream,
                                  ListKind kind);
 hipError_t launch_list_scan(const ListWork& w, int64_t n, int64_t* offsets, int64_t capacity, hipStream_t stream);
 hipError_t launch_list_offsets(int64_t n, int64_t* offsets, const ListWork& w, int64_t capacity,
                                bool want_voxels, hipStream_t stream);
 hipError_t launch_list_voxels(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
-                              const ListWork& w, int16_t* voxels, int64_t capacity,
-                              int64_t tiles_to_launch, hipStream_t stream);
+                              const ListWork& w, int16_t* voxels, int64_t tiles, hipStream_t stream);
 hipError_t launch_list_voxels32(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
-                                const ListWork& w, int32_t* voxels, int64_t tiles_to_launch, hipStream_t stream);
+                                const ListWork& w, int32_t* voxels, int64_t tiles, hipStream_t stream);
+// Few segments with room for few voxels: offsets, header and voxels in one
+// launch (Chebyshev lists).
+bool list_one_launch(int64_t n, int64_t capacity);
+hipError_t launch_list_all(const int32_t* segs, int64_t n, bool aligned8, int64_t* offsets, const ListWork& w,
+                           void* voxels, int64_t capacity, hipStream_t stream, ListKind kind);
 hipError_t launch_list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
                                      const ListWork& w, int16_t* voxels, hipStream_t stream);
 

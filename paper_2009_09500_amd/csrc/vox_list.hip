@@ -336,23 +336,24 @@ __global__ __launch_bounds__(kCountBlock) void k_list_offsets(
 
 // ---------------------------------------------------- one-block lists
 
-// Lists of at most kSegsPerCountBlock segments: the count, scan and offsets
-// kernels in one block (a call is then two launches with the voxel kernel).
-// Writes what those three write: counts, offsets[0..n], the total, the
-// status word (range flags, capacity) and the tile map (here tile-parallel).
+// A block's offsets of at most kSegsPerCountBlock segments: thread t's are
+// kCountPerThread t and the ones after, c their counts and off their offsets.
+// Returns the status (stored by one block) and the total.
 template <bool kAligned8, int kKind>
-__global__ __launch_bounds__(kCountBlock) void k_list_one_block(
-    const int32_t* __restrict__ segs, int64_t n, uint32_t* __restrict__ counts, int64_t* __restrict__ offsets,
-    int32_t* __restrict__ tile_seg, int64_t tile_limit, int64_t* __restrict__ total_p,
-    int32_t* __restrict__ status, int64_t capacity) {
+__device__ __forceinline__ int32_t one_block_offsets(const int32_t* __restrict__ segs, int64_t n,
+                                                     const uint32_t* __restrict__ counts, int64_t capacity,
+                                                     bool store, int64_t* __restrict__ offsets,
+                                                     int64_t* __restrict__ total_p, int32_t* __restrict__ status,
+                                                     int64_t (&c)[kCountPerThread], int64_t (&off)[kCountPerThread],
+                                                     int32_t& flags, int64_t& total) {
     __shared__ int64_t lds[kCountBlock / kWave];
-    __shared__ int64_t soff[kSegsPerCountBlock + 1];
-    int64_t c[kCountPerThread];
+    int64_t sum = 0;
     int32_t flag = 0;
 #pragma unroll
     for (int s = 0; s < kCountPerThread; ++s) {
-        const int64_t i = (int64_t)s * kCountBlock + threadIdx.x;
+        const int64_t i = (int64_t)threadIdx.x * kCountPerThread + s;
         c[s] = 0;
+        off[s] = sum;
         if (i < n) {
             Seg g = load_seg<kAligned8>(segs, i);
             const bool inr = kKind == kListI32 ? span_below_2p30(g) : in_int16(g);
@@ -364,68 +365,38 @@ __global__ __launch_bounds__(kCountBlock) void k_list_one_block(
             }
             flag |= (inr ? 0 : kStatusOutOfRange) | (list_long<kKind>(g) ? kListLong : 0);
             c[s] = v > 0xFFFFFFFFll ? 0xFFFFFFFFll : v;
-            counts[i] = (uint32_t)c[s];
         }
+        sum += c[s];
     }
-    const int32_t flags = block_or<kCountBlock>(flag, lds);
-    // Offsets, as the scan and offsets kernels would write them.
-    int64_t carry = 0;
-    int64_t off[kCountPerThread];
+    flags = block_or<kCountBlock>(flag, lds);
+    const int64_t ex = block_exclusive_sum<kCountBlock>(sum, lds, total);
+    const bool writer = store && threadIdx.x == 0;
+    const int32_t st = list_status(flags, total, capacity, writer ? status : nullptr);
 #pragma unroll
     for (int s = 0; s < kCountPerThread; ++s) {
-        int64_t sub;
-        off[s] = carry + block_exclusive_sum<kCountBlock>(c[s], lds, sub);
-        const int64_t i = (int64_t)s * kCountBlock + threadIdx.x;
-        if (i < n) {
-            offsets[i] = off[s];
-            soff[i] = off[s];
-        }
-        carry += sub;
+        const int64_t i = (int64_t)threadIdx.x * kCountPerThread + s;
+        off[s] += ex;
+        if (store && i < n) offsets[i] = off[s];
     }
-    const int64_t tot = carry;
-    const int32_t st = list_status(flags, tot, capacity, threadIdx.x == 0 ? status : nullptr);
-    if (threadIdx.x == 0) {
-        offsets[n] = tot;
-        *total_p = tot;
+    if (writer) {
+        offsets[n] = total;
+        *total_p = total;
     }
-    __syncthreads();  // soff complete
-    if (tile_limit > 0 && st == 0) {
-        // Tile t starts in the segment holding voxel t * kListTile: the
-        // largest i with offsets[i] <= t * kListTile (every segment has at
-        // least one voxel, so the offsets increase strictly).  One tile per
-        // thread at a time, so one long segment spreads over the block.
-        const int64_t ntiles = tot < tile_limit * kListTile ? (tot + kListTile - 1) / kListTile : tile_limit;
-        for (int64_t t = threadIdx.x; t < ntiles; t += kCountBlock) {
-            const int64_t j = t * kListTile;
-            int lo = 0, hi = (int)n - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (soff[mid] <= j) lo = mid; else hi = mid - 1;
-            }
-            tile_seg[t] = lo;
-        }
-    }
+    return st;
 }
 
-// Tile map for many tiles, one thread per tile: tile t starts in the
-// segment holding voxel t * kListTile, the largest i with offsets[i] <=
-// t * kListTile (found by binary search over the n offsets).
-__global__ __launch_bounds__(kCountBlock) void k_list_tiles(const int64_t* __restrict__ offsets, int64_t n,
-                                                            int32_t* __restrict__ tile_seg, int64_t tile_limit,
-                                                            const int64_t* __restrict__ total_p,
-                                                            const int32_t* __restrict__ status) {
-    if (*status != 0) return;
-    const int64_t tot = *total_p;
-    const int64_t ntiles = tot < tile_limit * kListTile ? (tot + kListTile - 1) / kListTile : tile_limit;
-    const int64_t t = (int64_t)blockIdx.x * kCountBlock + threadIdx.x;
-    if (t >= ntiles) return;
-    const int64_t j = t * kListTile;
-    int64_t lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (offsets[mid] <= j) lo = mid; else hi = mid - 1;
-    }
-    tile_seg[t] = (int32_t)lo;
+// Lists of at most kSegsPerCountBlock segments: the count, scan and offsets
+// kernels in one block (a call is then two launches with the voxel kernel).
+// Writes offsets[0..n], the total and the status word (range flags, capacity).
+template <bool kAligned8, int kKind>
+__global__ __launch_bounds__(kCountBlock) void k_list_one_block(
+    const int32_t* __restrict__ segs, int64_t n, const uint32_t* __restrict__ counts,
+    int64_t* __restrict__ offsets, int64_t* __restrict__ total_p, int32_t* __restrict__ status,
+    int64_t capacity) {
+    int64_t c[kCountPerThread], off[kCountPerThread], total;
+    int32_t flags;
+    one_block_offsets<kAligned8, kKind>(segs, n, counts, capacity, true, offsets, total_p, status, c, off, flags,
+                                        total);
 }
 
 // ------------------------------------------------------------ voxel tiles
@@ -457,6 +428,35 @@ struct SegStart {
 };
 constexpr int kWinSegs = 256;
 
+// How a tile finds its segments.
+enum ListTiles {
+    kTileMap,     // in the tile map (k_list_offsets)
+    kTileSearch,  // by a search of the offsets, 64 of them at a time: two rounds
+                  // up to 4096 segments; the map costs a launch (1024 int32
+                  // segments of 20 000 voxels: 0.0541 ms a call with it,
+                  // 0.0514 without)
+    kTileAll,     // every block computes all offsets (one_block_offsets) and
+                  // block 0 stores them: the call is one launch
+};
+
+// The segments of voxels j and k >= j: the largest i with offsets[i] <= j, and
+// k's.  All lanes of a wave take part.
+__device__ __forceinline__ void find_segments(const int64_t* __restrict__ offsets, int64_t n, int64_t j, int64_t k,
+                                              int32_t& sj, int32_t& sk) {
+    int64_t at = 0, bt = 0, len = n;
+    while (len > 1) {
+        const int64_t step = (len + kWave - 1) / kWave;
+        const int64_t a = at + step * (int64_t)__lane_id(), b = bt + step * (int64_t)__lane_id();
+        const int64_t va = offsets[a < n ? a : n], vb = offsets[b < n ? b : n];
+        // (Sample 0 is at or below; the others in order, offsets[n] above.)
+        at += step * (__popcll(__builtin_amdgcn_ballot_w64(va <= j)) - 1);
+        bt += step * (__popcll(__builtin_amdgcn_ballot_w64(vb <= k)) - 1);
+        len = step;
+    }
+    sj = (int32_t)at;
+    sk = (int32_t)bt;
+}
+
 // The high halves of two words, in one.
 __device__ __forceinline__ uint32_t high_halves(int32_t lo, int32_t hi) {
     return __builtin_amdgcn_perm((uint32_t)hi, (uint32_t)lo, 0x07060302u);
@@ -473,16 +473,24 @@ struct SegFix {
     int32_t pad[2];
 };
 
+// What a call of one launch stores besides its voxels.
+struct ListHeader {
+    int64_t* offsets;
+    int64_t* total;
+    int32_t* status;
+    int64_t capacity;
+};
+
 // T = int16_t: coordinates in int16 (differences below 2^16); T = int32_t:
 // every axis difference below 2^30 (checked by the count kernel).  The int16
 // kernel is held to 64 VGPRs (eight waves a SIMD, which its 13 KiB of LDS
 // allows); the int32 kernel's 25 KiB of LDS allows six blocks a CU anyway.
-template <bool kAligned8, typename T>
+template <bool kAligned8, typename T, ListTiles kTiles>
 __global__ __launch_bounds__(kListBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 8 : 1)))
 void k_list_voxels(
     const int32_t* __restrict__ segs, int64_t n, const int64_t* __restrict__ offsets,
     const int32_t* __restrict__ tile_seg, T* __restrict__ voxels,
-    const int64_t* __restrict__ total_p, const int32_t* __restrict__ status) {
+    const int64_t* __restrict__ total_p, const int32_t* __restrict__ status, ListHeader header) {
     constexpr int kSegWords = (int)(kWinSegs * sizeof(SegStart) / 4);
     constexpr int kVoxBytes = 3 * (int)sizeof(T);
     constexpr int kLaneWords = kListPerThread * kVoxBytes / 4;  // a lane's staged voxels
@@ -492,23 +500,66 @@ void k_list_voxels(
     // 25 KiB for int32 lists.
     __shared__ __align__(16) uint32_t lds_raw[kSegWords > kStageWords ? kSegWords : kStageWords];
     __shared__ int32_t srel[kWinSegs + 1];
+    __shared__ int32_t srel_all[kTiles == kTileAll ? kSegsPerCountBlock + 1 : 1];
     SegStart* sseg = reinterpret_cast<SegStart*>(lds_raw);
     SegFix* sfix = reinterpret_cast<SegFix*>(lds_raw);
     uint32_t* stage = lds_raw;
     static_assert(sizeof(SegStart) % 16 == 0 && sizeof(SegFix) % 16 == 0 && (kListPerThread * kVoxBytes) % 4 == 0, "packing");
 
-    // The header and the tile's entries, loaded together (the map has an entry
-    // more than the launch has tiles): one round trip before the segments'.
     const int64_t tile = blockIdx.x;
-    const int64_t total = *total_p;
-    const int32_t st0 = status[0], long_segs = status[1];
-    const int32_t s0 = tile_seg[tile], after = tile_seg[tile + 1];
     const int64_t j0 = tile * kListTile;
-    asm volatile("" ::"s"(total), "s"(long_segs), "s"(s0), "s"(after));  // (all loaded before the first wait)
-    if (st0 != 0 || j0 >= total) return;
-    const int64_t j1 = j0 + kListTile < total ? j0 + kListTile : total;
-    const int64_t ntiles = (total + kListTile - 1) / kListTile;
-    const int32_t s1 = tile + 1 < ntiles ? after : (int32_t)(n - 1);
+    // An offset relative to j0 (a tile's own segments start within
+    // [-(2^30 - 1), kListTile]).
+    auto relative = [&](int64_t o) {
+        const int64_t rel = o - j0;
+        return (int32_t)(rel < -(1ll << 30) ? -(1ll << 30) : (rel > (1ll << 30) ? (1ll << 30) : rel));
+    };
+    int64_t total, j1;
+    int32_t s0, s1, long_segs;
+    if constexpr (kTiles == kTileAll) {
+        __shared__ int32_t ends[2];
+        int64_t c[kCountPerThread], off[kCountPerThread];
+        int32_t flags;
+        const int32_t st = one_block_offsets<kAligned8, sizeof(T) == 2 ? kListI16 : kListI32>(
+            segs, n, nullptr, header.capacity, blockIdx.x == 0, header.offsets, header.total, header.status, c, off,
+            flags, total);
+        if (st != 0 || j0 >= total) return;
+        j1 = j0 + kListTile < total ? j0 + kListTile : total;
+#pragma unroll
+        for (int i = 0; i < kCountPerThread; ++i) {
+            const int32_t si = threadIdx.x * kCountPerThread + i;
+            if (si < n) {
+                srel_all[si] = relative(off[i]);
+                if (off[i] <= j0 && j0 < off[i] + c[i]) ends[0] = si;
+                if (off[i] < j1 && j1 <= off[i] + c[i]) ends[1] = si;
+            }
+        }
+        if (threadIdx.x == 0) srel_all[n] = relative(total);
+        __syncthreads();
+        s0 = __builtin_amdgcn_readfirstlane(ends[0]);
+        s1 = __builtin_amdgcn_readfirstlane(ends[1]);
+        long_segs = flags & kListLong;
+    } else {
+        // The header and the tile's entries, loaded together (the map has an
+        // entry more than the launch has tiles): one round trip before the
+        // segments'.
+        total = *total_p;
+        const int32_t st0 = status[0];
+        long_segs = status[1];
+        if constexpr (kTiles == kTileMap) {
+            s0 = tile_seg[tile];
+            s1 = tile_seg[tile + 1];
+            asm volatile("" ::"s"(total), "s"(long_segs), "s"(s0), "s"(s1));  // (all loaded before the first wait)
+            if (st0 != 0 || j0 >= total) return;
+            j1 = j0 + kListTile < total ? j0 + kListTile : total;
+            const int64_t ntiles = (total + kListTile - 1) / kListTile;
+            if (tile + 1 >= ntiles) s1 = (int32_t)(n - 1);
+        } else {
+            if (st0 != 0 || j0 >= total) return;
+            j1 = j0 + kListTile < total ? j0 + kListTile : total;
+            find_segments(offsets, n, j0, j1 - 1, s0, s1);
+        }
+    }
     const int nseg = s1 - s0 + 1;  // <= kListTile + 1
 
     const int first = threadIdx.x * kListPerThread;  // tile-relative voxel
@@ -521,12 +572,12 @@ void k_list_voxels(
     // every tile is one window (kOne: every voxel of the lane's P lies in it).
     auto stage_offsets = [&](int w, int m) {
         for (int i = threadIdx.x; i <= m; i += kListBlock) {
-            const int64_t si = (int64_t)s0 + w + i;
-            int64_t o = si <= n ? offsets[si] : total;
-            int64_t rel = o - j0;
-            // A tile's own segments start within [-(2^30 - 1), kListTile].
-            rel = rel < -(1ll << 30) ? -(1ll << 30) : (rel > (1ll << 30) ? (1ll << 30) : rel);
-            srel[i] = (int32_t)rel;
+            if constexpr (kTiles == kTileAll) {
+                srel[i] = srel_all[s0 + w + i];
+            } else {
+                const int64_t si = (int64_t)s0 + w + i;
+                srel[i] = relative(si <= n ? offsets[si] : total);
+            }
         }
     };
     // This lane's voxels [lo, hi) inside the window and the staged segment of
@@ -1202,38 +1253,35 @@ hipError_t launch_list_count(const int32_t* segs, int64_t n, bool aligned8, cons
     return hipGetLastError();
 }
 
-// Tile maps up to this many tiles are written by the one-block kernel
-// itself; larger ones by k_list_tiles, one thread per tile.
-constexpr int64_t kOneBlockMaxTiles = 4096;
-
 template <int kKind>
 static void list_one_block(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w, int64_t* offsets,
-                           int64_t capacity, bool want_voxels, hipStream_t stream) {
-    // (The Euclidean lists are written per segment: no output tiles.)
-    const int64_t tiles = want_voxels && kKind != kListEuclid ? (capacity + kListTile - 1) / kListTile : 0;
-    const int64_t tile_limit = tiles <= kOneBlockMaxTiles ? tiles : 0;
+                           int64_t capacity, hipStream_t stream) {
     if (kKind == kListEuclid && n > 0) launch_euclid_counts(segs, n, aligned8, w, stream);
     if (aligned8)
-        k_list_one_block<true, kKind><<<1, kCountBlock, 0, stream>>>(segs, n, w.counts, offsets, w.tile_seg,
-                                                                      tile_limit, w.total, w.status, capacity);
+        k_list_one_block<true, kKind><<<1, kCountBlock, 0, stream>>>(segs, n, w.counts, offsets, w.total, w.status,
+                                                                      capacity);
     else
-        k_list_one_block<false, kKind><<<1, kCountBlock, 0, stream>>>(segs, n, w.counts, offsets, w.tile_seg,
-                                                                       tile_limit, w.total, w.status, capacity);
-    if (tiles > kOneBlockMaxTiles)
-        k_list_tiles<<<dim3((unsigned)((tiles + kCountBlock - 1) / kCountBlock)), kCountBlock, 0, stream>>>(
-            offsets, n, w.tile_seg, tiles, w.total, w.status);
+        k_list_one_block<false, kKind><<<1, kCountBlock, 0, stream>>>(segs, n, w.counts, offsets, w.total,
+                                                                       w.status, capacity);
 }
 
+// Whether the tiles of a list with room for this many search for their
+// segments, or find them in the map.
+static bool list_searches(int64_t n, int64_t tiles) { return n <= kSegsPerCountBlock || tiles > 4 * n; }
+
+// Lists of one launch: up to two blocks a CU, each of which computes all
+// offsets (1000 segments, 70 tiles: 0.0116 -> 0.0082 ms a call, its host time).
+constexpr int64_t kOneLaunchMaxTiles = 512;
+
 hipError_t launch_list_one_block(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w,
-                                 int64_t* offsets, int64_t capacity, bool want_voxels, hipStream_t stream,
-                                 ListKind kind) {
+                                 int64_t* offsets, int64_t capacity, hipStream_t stream, ListKind kind) {
     KernelTimer timer("list_one_block", stream);
     if (kind == kListEuclid)
-        list_one_block<kListEuclid>(segs, n, aligned8, w, offsets, capacity, want_voxels, stream);
+        list_one_block<kListEuclid>(segs, n, aligned8, w, offsets, capacity, stream);
     else if (kind == kListI32)
-        list_one_block<kListI32>(segs, n, aligned8, w, offsets, capacity, want_voxels, stream);
+        list_one_block<kListI32>(segs, n, aligned8, w, offsets, capacity, stream);
     else
-        list_one_block<kListI16>(segs, n, aligned8, w, offsets, capacity, want_voxels, stream);
+        list_one_block<kListI16>(segs, n, aligned8, w, offsets, capacity, stream);
     return hipGetLastError();
 }
 
@@ -1250,51 +1298,68 @@ hipError_t launch_list_offsets(int64_t n, int64_t* offsets, const ListWork& w, i
                                bool want_voxels, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     const int64_t tiles = want_voxels ? (capacity + kListTile - 1) / kListTile : 0;
-    // Segments of more than four tiles on average: the tile map from
-    // k_list_tiles (one thread per tile) rather than one thread per segment.
-    const bool per_tile = tiles > 4 * n;
+    // (No map for segments of more than four tiles on average, whose runs of
+    // entries a thread each would write: the tiles search.)
+    const int64_t mapped = list_searches(n, tiles) ? 0 : tiles;
     KernelTimer timer("list_offsets", stream);
     if (w.nb <= kFusedScanMaxBlocks)
         k_list_offsets<true><<<dim3((unsigned)w.nb), kCountBlock, 0, stream>>>(
-            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, per_tile ? 0 : tiles,
+            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped,
             w.total, w.status);
     else
         k_list_offsets<false><<<dim3((unsigned)w.nb), kCountBlock, 0, stream>>>(
-            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, per_tile ? 0 : tiles,
+            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped,
             w.total, w.status);
-    if (per_tile)
-        k_list_tiles<<<dim3((unsigned)((tiles + kCountBlock - 1) / kCountBlock)), kCountBlock, 0, stream>>>(
-            offsets, n, w.tile_seg, tiles, w.total, w.status);
+    return hipGetLastError();
+}
+
+template <typename T, ListTiles kTiles>
+static void list_voxels(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets, const ListWork& w,
+                        T* voxels, int64_t tiles, const ListHeader& header, hipStream_t stream) {
+    if (aligned8)
+        k_list_voxels<true, T, kTiles><<<dim3((unsigned)tiles), kListBlock, 0, stream>>>(
+            segs, n, offsets, w.tile_seg, voxels, w.total, w.status, header);
+    else
+        k_list_voxels<false, T, kTiles><<<dim3((unsigned)tiles), kListBlock, 0, stream>>>(
+            segs, n, offsets, w.tile_seg, voxels, w.total, w.status, header);
+}
+
+template <typename T>
+static hipError_t launch_tiles(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
+                               const ListWork& w, T* voxels, int64_t tiles, hipStream_t stream) {
+    if (n == 0 || tiles <= 0) return hipSuccess;
+    KernelTimer timer(sizeof(T) == 2 ? "list_voxels" : "list_voxels32", stream);
+    if (list_searches(n, w.ntiles))
+        list_voxels<T, kTileSearch>(segs, n, aligned8, offsets, w, voxels, tiles, ListHeader{}, stream);
+    else
+        list_voxels<T, kTileMap>(segs, n, aligned8, offsets, w, voxels, tiles, ListHeader{}, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_list_voxels(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
-                              const ListWork& w, int16_t* voxels, int64_t capacity,
-                              int64_t tiles_to_launch, hipStream_t stream) {
-    (void)capacity;
-    if (n == 0 || tiles_to_launch <= 0) return hipSuccess;
-    dim3 grid((unsigned)tiles_to_launch);
-    KernelTimer timer("list_voxels", stream);
-    if (aligned8)
-        k_list_voxels<true, int16_t><<<grid, kListBlock, 0, stream>>>(segs, n, offsets, w.tile_seg, voxels,
-                                                                      w.total, w.status);
-    else
-        k_list_voxels<false, int16_t><<<grid, kListBlock, 0, stream>>>(segs, n, offsets, w.tile_seg, voxels,
-                                                                       w.total, w.status);
-    return hipGetLastError();
+                              const ListWork& w, int16_t* voxels, int64_t tiles, hipStream_t stream) {
+    return launch_tiles(segs, n, aligned8, offsets, w, voxels, tiles, stream);
 }
 
 hipError_t launch_list_voxels32(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
-                                const ListWork& w, int32_t* voxels, int64_t tiles_to_launch, hipStream_t stream) {
-    if (n == 0 || tiles_to_launch <= 0) return hipSuccess;
-    dim3 grid((unsigned)tiles_to_launch);
-    KernelTimer timer("list_voxels32", stream);
-    if (aligned8)
-        k_list_voxels<true, int32_t><<<grid, kListBlock, 0, stream>>>(segs, n, offsets, w.tile_seg, voxels,
-                                                                      w.total, w.status);
+                                const ListWork& w, int32_t* voxels, int64_t tiles, hipStream_t stream) {
+    return launch_tiles(segs, n, aligned8, offsets, w, voxels, tiles, stream);
+}
+
+bool list_one_launch(int64_t n, int64_t capacity) {
+    return n >= 1 && n <= kSegsPerCountBlock && capacity <= kOneLaunchMaxTiles * kListTile;
+}
+
+hipError_t launch_list_all(const int32_t* segs, int64_t n, bool aligned8, int64_t* offsets, const ListWork& w,
+                           void* voxels, int64_t capacity, hipStream_t stream, ListKind kind) {
+    KernelTimer timer("list_all", stream);
+    const ListHeader header{offsets, w.total, w.status, capacity};
+    if (kind == kListI32)
+        list_voxels<int32_t, kTileAll>(segs, n, aligned8, offsets, w, static_cast<int32_t*>(voxels), w.ntiles,
+                                       header, stream);
     else
-        k_list_voxels<false, int32_t><<<grid, kListBlock, 0, stream>>>(segs, n, offsets, w.tile_seg, voxels,
-                                                                       w.total, w.status);
+        list_voxels<int16_t, kTileAll>(segs, n, aligned8, offsets, w, static_cast<int16_t*>(voxels), w.ntiles,
+                                       header, stream);
     return hipGetLastError();
 }
 

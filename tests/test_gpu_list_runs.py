@@ -6,6 +6,9 @@ and one sample more, few long segments, and segments of every kind in turn."""
 import numpy as np
 import pytest
 
+from oracle import oracle
+from paper_2009_09500_amd import binding
+from tests.gpu_helpers import dev, to_dev, to_host
 from tests.test_gpu_euclid import assert_list
 from tests.test_gpu_list import assert_parity
 
@@ -63,3 +66,30 @@ def test_euclid_lanes(lanes):
 def test_euclid_long_segments(n):
     rng = np.random.default_rng(n)
     assert_list(axis_aligned_mix(rng, rng.integers(1200, 2000, n)))
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("n,room", [(1, 1), (3, 512 * 2048), (1024, 512 * 2048), (1024, 512 * 2048 + 1), (1025, 1),
+                                    (4097, 1)])
+def test_list_of_few_segments(n, room, wide):
+    """One launch (up to 1024 segments, 512 tiles of room), the search by tile
+    (one segment of many tiles among short ones), and the tile map."""
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(n + room)
+    lengths = rng.integers(0, 9, n)
+    lengths[n // 2] = 30000 if n > 1024 or n == 1 else 2047 - int(lengths[: n // 2].sum() + n // 2) % 2048
+    segs = axis_aligned_mix(rng, lengths)
+    total = int(oracle.offsets(segs)[-1])
+    expect = oracle.voxel_list(segs)
+    for capacity in (max(room, total), max(room, total) * 5 * n):
+        if capacity > 1 << 26:
+            continue
+        vox = torch.full((capacity * 3 + 64,), 77, dtype=torch.int32 if wide else torch.int16, device=dev())
+        offs = torch.empty(n + 1, dtype=torch.int64, device=dev())
+        work = binding.workspace(binding.vox_list_workspace_bytes(n, capacity), dev())
+        binding.vox_segments_to_list(to_dev(segs), offs, vox[: capacity * 3].view(-1, 3), capacity, work, wide=wide)
+        assert binding.vox_read_status(work) == 0
+        assert np.array_equal(to_host(offs), oracle.offsets(segs))
+        got = to_host(vox)
+        assert np.array_equal(got[: 3 * total].reshape(-1, 3), expect)
+        assert np.all(got[3 * total:] == 77)
