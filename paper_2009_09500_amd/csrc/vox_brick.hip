@@ -489,26 +489,34 @@ struct Stage {
 };
 static_assert(kOrderBins == 64 && kMaxWalkParts == 8, "walk classes: buckets 0, 1-32, 33-48, 49-63");
 constexpr int kBinEnd8 = 0, kBinEnd4 = 32, kBinEnd2 = 48;  // last bucket of each class
+// ... and of the walks of three pieces and more, and of two (estimates of one
+// and two are exact).
+constexpr int kBinEnd3 = kOrderBins - 3, kBinPairs = kOrderBins - 2;
 
-__device__ __forceinline__ uint32_t order_bin(const StagedSeg& g, const BrickGeom& bg) {
-    const int32_t p0[3] = {g.p0[0], g.p0[1], g.p0[2]}, p1[3] = {g.p1[0], g.p1[1], g.p1[2]};
-    const uint32_t est = walk_estimate(p0, p1, bg.lg);
+__device__ __forceinline__ uint32_t order_bin(uint32_t est) {
     return (uint32_t)kOrderBins - (est < (uint32_t)kOrderBins ? est : (uint32_t)kOrderBins);
+}
+
+__device__ __forceinline__ uint32_t brick_of(const BrickGeom& bg, int32_t bx, int32_t by, int32_t bz) {
+    return __umul24(__umul24((uint32_t)bz, (uint32_t)bg.nb[1]) + (uint32_t)by, (uint32_t)bg.nb[0]) + (uint32_t)bx;
 }
 
 // Loads segments [base, base + cnt) into the stage (all threads of the
 // block), writes counts, flags out-of-volume segments, and builds the order
-// of the in-volume ones.
-template <int kN>
+// of the in-volume ones, except those of which direct(segment, estimate) says
+// that it has dealt with them.
+template <int kN, typename Direct>
 __device__ __forceinline__ void stage_segments(const int32_t* __restrict__ segs, int64_t base, uint32_t cnt,
                                                const BrickGeom& bg, bool euclid, Stage<kN>& st,
-                                               int32_t* __restrict__ counts, bool& bad) {
+                                               int32_t* __restrict__ counts, bool& bad, Direct direct) {
     if (threadIdx.x < kOrderBins) st.bins[threadIdx.x] = 0;
     lds_barrier();
-    // Bit t of `mine` marks this thread's t-th segment as in the volume.
-    uint32_t mine = 0;
-    int slot = 0;
-    for (uint32_t t = threadIdx.x; t < cnt; t += kHistBlock, ++slot) {
+    constexpr int kSlots = kN / kHistBlock;
+    uint32_t bins[(kSlots + 3) / 4] = {};  // bin + 1 of each of this thread's segments, 0: none
+#pragma unroll
+    for (int slot = 0; slot < kSlots; ++slot) {
+        const uint32_t t = threadIdx.x + (uint32_t)slot * kHistBlock;
+        if (t >= cnt) continue;
         const Seg g = load_seg<true>(segs, base + t);
         const bool inside = in_volume(g, bg);
         if (counts) {
@@ -528,10 +536,14 @@ __device__ __forceinline__ void stage_segments(const int32_t* __restrict__ segs,
             s.p0[ax] = (uint16_t)g.p0[ax];
             s.p1[ax] = (uint16_t)g.p1[ax];
         }
-        st.seg[t] = s;
         if (inside) {
-            mine |= 1u << slot;
-            atomicAdd(&st.bins[order_bin(s, bg)], 1u);
+            const uint32_t est = walk_estimate(g.p0, g.p1, bg.lg);
+            if (!direct(g, est)) {
+                const uint32_t bin = order_bin(est);
+                st.seg[t] = s;
+                bins[slot / 4] |= (bin + 1u) << (8 * (slot % 4));
+                atomicAdd(&st.bins[bin], 1u);
+            }
         } else {
             bad = true;
         }
@@ -547,17 +559,18 @@ __device__ __forceinline__ void stage_segments(const int32_t* __restrict__ segs,
         }
     }
     lds_barrier();
-    slot = 0;
-    for (uint32_t t = threadIdx.x; t < cnt; t += kHistBlock, ++slot) {
-        if (mine & (1u << slot)) {
-            const uint32_t pos = atomicAdd(&st.bins[order_bin(st.seg[t], bg)], 1u);
-            st.order[pos] = (uint16_t)t;
+#pragma unroll
+    for (int slot = 0; slot < kSlots; ++slot) {
+        const uint32_t bin = (bins[slot / 4] >> (8 * (slot % 4))) & 255u;
+        if (bin != 0u) {
+            const uint32_t pos = atomicAdd(&st.bins[bin - 1u], 1u);
+            st.order[pos] = (uint16_t)(threadIdx.x + (uint32_t)slot * kHistBlock);
         }
     }
     lds_barrier();
 }
-static_assert(kStage / kHistBlock <= 32 && kStageBig / kHistBlock <= 32 && kStageBig <= 65536,
-              "one validity bit per staged segment and thread; 16-bit order entries");
+static_assert(kStage % kHistBlock == 0 && kStageBig % kHistBlock == 0 && kStageBig <= 65536,
+              "whole slots per thread; 16-bit order entries");
 
 struct WalkState {
     AxisCross c[3];
@@ -722,6 +735,11 @@ __device__ __forceinline__ void euclid_counts(const Stage<kN>& st, int32_t* __re
 // or three each at their start: the scatter, whose steps are dear (a record
 // store each), gains from them, the histogram (an LDS increment a step) does
 // not.
+// Segments of one and two pieces (with kSplit) are groups of their own, which
+// need no walk: no division, and one for the crossing.  The histogram counts
+// them while it stages.  With that, and divisions by biased reciprocals where
+// there were IEEE ones (six a walk), the histogram of 4 M segments of 4.5 pieces
+// takes 0.079 ms against 0.102, of 9.6 M of 2 pieces 0.165 against 0.210.
 // emit(maker, brick id, klo, khi, brick x, y, z) per piece, [klo, khi] being
 // the segment's k-window inside the brick; the Maker is made once per walk
 // from the segment and its N, so what a piece's record takes from the segment
@@ -729,6 +747,42 @@ __device__ __forceinline__ void euclid_counts(const Stage<kN>& st, int32_t* __re
 struct NoMaker {
     __device__ __forceinline__ NoMaker(const StagedSeg&, uint32_t) {}
 };
+
+// The two pieces of a segment that crosses one brick face, or its one piece.
+template <bool kPair, typename Maker, typename Emit>
+__device__ __forceinline__ void short_walk(const StagedSeg& g, const BrickGeom& bg, bool euclid, Emit emit) {
+    uint32_t N = 0, ss = 0, m = 0, as = 0, ns = 0;
+    int32_t b0[3], b1[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        const int32_t p0 = g.p0[ax], p1 = g.p1[ax], d = p1 - p0;
+        const uint32_t a = (uint32_t)(d < 0 ? -d : d);
+        N = a > N ? a : N;
+        ss += a * a;
+        b0[ax] = p0 >> bg.lg[ax];
+        b1[ax] = p1 >> bg.lg[ax];
+        if constexpr (kPair) {
+            // Offset of the far face from p0 on the crossing axis.
+            const bool cross = b0[ax] != b1[ax];
+            const uint32_t far = (uint32_t)(d < 0 ? p0 - (b0[ax] << bg.lg[ax]) + 1 : (b1[ax] << bg.lg[ax]) - p0);
+            m = cross ? far : m;
+            as = cross ? a : as;
+            ns = cross ? (d < 0 ? 1u : 0u) : ns;
+        }
+    }
+    if (euclid) N = isqrt31(ss);
+    const Maker maker(g, N);
+    uint32_t k = N + 1u;
+    if constexpr (kPair) {
+        uint32_t q, r;
+        const uint32_t D = 2u * as;
+        divmod_down(2u * __umul24(N, m) - N + ns, D, rcp_walk(D), q, r);
+        k = r ? q + 1u : q;
+    }
+    emit(maker, brick_of(bg, b0[0], b0[1], b0[2]), 0u, k - 1u, b0[0], b0[1], b0[2]);
+    if constexpr (kPair) emit(maker, brick_of(bg, b1[0], b1[1], b1[2]), k, N, b1[0], b1[1], b1[2]);
+}
+
 template <bool kSplit, typename Maker, int kN, typename Emit>
 __device__ __forceinline__ void walk_ordered(Stage<kN>& st, const BrickGeom& bg, bool euclid, Emit emit) {
     const uint32_t lane = __lane_id();
@@ -738,15 +792,33 @@ __device__ __forceinline__ void walk_ordered(Stage<kN>& st, const BrickGeom& bg,
     const uint32_t e8 = kSplit ? st.bins[kBinEnd8] : 0u;
     const uint32_t e4 = kSplit ? st.bins[kBinEnd4] : 0u;
     const uint32_t e2 = kSplit ? st.bins[kBinEnd2] : 0u;
+    const uint32_t e1 = kSplit ? st.bins[kBinEnd3] : nvalid;
+    const uint32_t ep = kSplit ? st.bins[kBinPairs] : nvalid;
     const uint32_t g4 = (e8 + 7u) >> 3;
     const uint32_t g2 = g4 + ((e4 - e8 + 15u) >> 4);
     const uint32_t g1 = g2 + ((e2 - e4 + 31u) >> 5);
-    const uint32_t gt = g1 + ((nvalid - e2 + 63u) >> 6);
+    const uint32_t gp = g1 + ((e1 - e2 + 63u) >> 6);
+    const uint32_t gs = gp + ((ep - e1 + 63u) >> 6);
+    const uint32_t gt = gs + ((nvalid - ep + 63u) >> 6);
     for (;;) {
         uint32_t grp = 0;
         if (lane == 0) grp = atomicAdd(&st.claim, 1u);
         grp = __builtin_amdgcn_readfirstlane(grp);
         if (grp >= gt) break;
+        if constexpr (kSplit) {
+            if (grp >= gp) {
+                const bool pair = grp < gs;
+                const uint32_t i = (pair ? e1 + ((grp - gp) << 6) : ep + ((grp - gs) << 6)) + lane;
+                if (i < (pair ? ep : nvalid)) {
+                    const StagedSeg g = st.seg[st.order[i]];
+                    if (pair)
+                        short_walk<true, Maker>(g, bg, euclid, emit);
+                    else
+                        short_walk<false, Maker>(g, bg, euclid, emit);
+                }
+                continue;
+            }
+        }
         uint32_t lgp, start, end;
         if (grp < g4) {
             lgp = 3; start = grp << 3; end = e8;
@@ -755,7 +827,7 @@ __device__ __forceinline__ void walk_ordered(Stage<kN>& st, const BrickGeom& bg,
         } else if (grp < g1) {
             lgp = 1; start = e4 + ((grp - g2) << 5); end = e2;
         } else {
-            lgp = 0; start = e2 + ((grp - g1) << 6); end = nvalid;
+            lgp = 0; start = e2 + ((grp - g1) << 6); end = e1;
         }
         const uint32_t i = start + (lane >> lgp);
         bool active = i < end;
@@ -772,10 +844,8 @@ __device__ __forceinline__ void walk_ordered(Stage<kN>& st, const BrickGeom& bg,
             const bool more = km <= w.kend;
             // Brick ids and counts stay below 2^24: 24-bit multiplies.
             if (active)
-                emit(maker, __umul24(__umul24((uint32_t)w.c[2].b, (uint32_t)bg.nb[1]) + (uint32_t)w.c[1].b,
-                              (uint32_t)bg.nb[0]) +
-                         (uint32_t)w.c[0].b,
-                     w.klo, more ? km - 1u : w.kend, w.c[0].b, w.c[1].b, w.c[2].b);
+                emit(maker, brick_of(bg, w.c[0].b, w.c[1].b, w.c[2].b), w.klo, more ? km - 1u : w.kend, w.c[0].b,
+                     w.c[1].b, w.c[2].b);
             // The rest with selects only (lanes step different segments).
             const bool go = active && more;
 #pragma unroll
@@ -799,7 +869,16 @@ __device__ __forceinline__ void hist_row(const BrickScene& sc, uint32_t g, Stage
     bool bad = false;
     for (int64_t base = lo; base < hi; base += kN) {
         const uint32_t cnt = (uint32_t)(hi - base < kN ? hi - base : kN);
-        stage_segments(sc.segs, base, cnt, bg, euclid, st, sc.counts, bad);
+        // Segments of one and two pieces, which lie in the bricks of their end
+        // points, are counted on the way (unless euclid_counts wants them).
+        auto ends = [&](const Seg& g, uint32_t est) {
+            if (est > 2u || (euclid && sc.counts)) return false;
+            atomicAdd(&lh[brick_of(bg, g.p0[0] >> bg.lg[0], g.p0[1] >> bg.lg[1], g.p0[2] >> bg.lg[2])], 1u);
+            if (est == 2u)
+                atomicAdd(&lh[brick_of(bg, g.p1[0] >> bg.lg[0], g.p1[1] >> bg.lg[1], g.p1[2] >> bg.lg[2])], 1u);
+            return true;
+        };
+        stage_segments(sc.segs, base, cnt, bg, euclid, st, sc.counts, bad, ends);
         walk_ordered<false, NoMaker>(st, bg, euclid,
                                      [&](const NoMaker&, uint32_t b, uint32_t, uint32_t, int32_t, int32_t, int32_t) {
                                          atomicAdd(&lh[b], 1u);
@@ -1250,7 +1329,8 @@ __global__ __launch_bounds__(kHistBlock) void k_brick_scatter(uint8_t* __restric
     bool bad = false;
     for (int64_t base = lo; base < hi; base += kStage) {
         const uint32_t cnt = (uint32_t)(hi - base < kStage ? hi - base : kStage);
-        stage_segments(sc.segs, base, cnt, bg, euclid, st, nullptr, bad);
+        stage_segments(sc.segs, base, cnt, bg, euclid, st, nullptr, bad,
+                       [](const Seg&, uint32_t) { return false; });
         auto place = [&](const auto& maker, uint32_t b, uint32_t klo, uint32_t khi, int32_t bx, int32_t by,
                          int32_t bz) {
             const uint32_t pos = atomicAdd(&cur[b], 1u);

@@ -29,21 +29,15 @@ __host__ __device__ __forceinline__ uint32_t div_ceil_u64(uint64_t x, uint32_t y
     return (uint32_t)((x + y - 1) / y);
 }
 
-// floor(x / y) and remainder, exact, same fast path.
-__host__ __device__ __forceinline__ void divmod_u64(uint64_t x, uint32_t y, uint32_t& q, uint32_t& r) {
-    if (x < (1ull << 24)) {
-        uint32_t xi = (uint32_t)x;
-        uint32_t qq = (uint32_t)((float)xi / (float)y);
-        int32_t rr = (int32_t)(xi - qq * y);
-        if (rr < 0) { qq -= 1; rr += (int32_t)y; }
-        else if (rr >= (int32_t)y) { qq += 1; rr -= (int32_t)y; }
-        q = qq;
-        r = (uint32_t)rr;
-        return;
-    }
-    uint64_t qq = x / y;
-    q = (uint32_t)qq;
-    r = (uint32_t)(x - qq * y);
+// floor(x / y) and remainder for x < 2^31, 1 <= y < 2^24 and quotients below
+// 2^19, by a reciprocal biased downwards (divmod_down): the walk's divisions.
+// Volume sides are at most 16384, so N and every k stay within 2^14.
+__host__ __device__ __forceinline__ float rcp_walk(uint32_t y) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return rcp_down(y);
+#else
+    return rcp_bias_down(1.0f / (float)y);
+#endif
 }
 
 constexpr uint32_t kNever = 0xFFFFFFFFu;
@@ -74,36 +68,28 @@ struct AxisCross {
 // axis coordinate at k0 and the next crossing after it.  The coordinate's
 // offset from p0 at k0 is eq. (3)'s quotient there, (2 k0 a + N - neg) div 2N
 // (k0 itself on an axis with a = N, 0 at k0 = 0); the next crossing is where
-// the offset reaches the brick's far face, m, measured from p0.
+// the offset reaches the brick's far face, m, measured from p0.  Without a
+// branch: an axis that crosses nothing computes crossings that are not used.
+// Likewise Q, R matter from the second crossing on, where a > B and Q < N.
 __host__ __device__ __forceinline__ void cross_init_at(AxisCross& c, int32_t p0, int32_t p1, uint32_t a,
                                                        uint32_t neg, uint32_t N, int lg, uint32_t k0) {
-    uint32_t off = 0;
-    if (a == N) {
-        off = k0;
-    } else if (a != 0 && k0 != 0) {
-        uint32_t r;
-        divmod_u64(2ull * k0 * a + N - neg, 2u * N, off, r);
+    uint32_t off = 0, r;
+    if (k0 != 0) {
+        const uint32_t two_n = 2u * N;
+        divmod_down(2u * mul_u24(k0, a) + N - neg, two_n, rcp_walk(two_n), off, r);
     }
     c.b = (neg ? p0 - (int32_t)off : p0 + (int32_t)off) >> lg;
     c.bend = p1 >> lg;
     c.dir = neg ? -1 : 1;
-    c.kn = kNever;
-    c.sl = c.Q = c.R = 0;
-    c.D = 1;
-    if (c.b == c.bend) return;
     const uint32_t m = neg ? (uint32_t)(p0 - (c.b << lg) + 1) : (uint32_t)(((c.b + 1) << lg) - p0);
-    const uint32_t B = 1u << lg;
-    if (a == N) {  // dominant axis: crossings exactly B apart
-        c.kn = m;
-        c.Q = B;
-        return;
-    }
-    c.D = 2u * a;
-    uint32_t q, r;
-    divmod_u64(2ull * N * m - N + neg, c.D, q, r);
-    c.kn = r ? q + 1u : q;
+    const uint32_t two_n = 2u * N;
+    c.D = a ? 2u * a : 1u;
+    const float rcp = rcp_walk(c.D);
+    uint32_t q;
+    divmod_down(mul_u24(two_n, m) - N + neg, c.D, rcp, q, r);
+    c.kn = c.b == c.bend ? kNever : (r ? q + 1u : q);
     c.sl = r ? c.D - r : 0u;
-    divmod_u64(2ull * N * B, c.D, c.Q, c.R);
+    divmod_down(two_n << lg, c.D, rcp, c.Q, c.R);
 }
 
 __host__ __device__ __forceinline__ void cross_init(AxisCross& c, int32_t p0, int32_t p1, uint32_t a,
@@ -201,8 +187,14 @@ __host__ __device__ __forceinline__ bool part_window(const int32_t p0[3], const 
     const int32_t b0 = q0 >> l;
     const uint32_t m0 = ns ? (uint32_t)(q0 - (b0 << l) + 1) : (uint32_t)(((b0 + 1) << l) - q0);
     const uint32_t B = 1u << l;
-    k0 = j0 == 0u ? 0u : k_reach(m0 + (j0 - 1u) * B, as, N, ns);
-    k1 = j1 == nbs ? N : k_reach(m0 + (j1 - 1u) * B, as, N, ns) - 1u;
+    // (Ceilings as in cross_init_at; as >= 1 where they are used.)
+    const uint32_t D = as ? 2u * as : 1u;
+    const float rcp = rcp_walk(D);
+    uint32_t q0k, r0k, q1k, r1k;
+    divmod_down(2u * mul_u24(N, m0 + (j0 - 1u) * B) - N + ns, D, rcp, q0k, r0k);
+    divmod_down(2u * mul_u24(N, m0 + (j1 - 1u) * B) - N + ns, D, rcp, q1k, r1k);
+    k0 = j0 == 0u ? 0u : q0k + (r0k ? 1u : 0u);
+    k1 = j1 == nbs ? N : q1k + (r1k ? 1u : 0u) - 1u;
     return true;
 }
 
