@@ -511,7 +511,7 @@ __device__ __forceinline__ void stage_segments(const int32_t* __restrict__ segs,
                                                int32_t* __restrict__ counts, bool& bad, Direct direct) {
     if (threadIdx.x < kOrderBins) st.bins[threadIdx.x] = 0;
     lds_barrier();
-    constexpr int kSlots = kN / kHistBlock;
+    constexpr int kSlots = (kN + kHistBlock - 1) / kHistBlock;
     uint32_t bins[(kSlots + 3) / 4] = {};  // bin + 1 of each of this thread's segments, 0: none
 #pragma unroll
     for (int slot = 0; slot < kSlots; ++slot) {
@@ -569,8 +569,7 @@ __device__ __forceinline__ void stage_segments(const int32_t* __restrict__ segs,
     }
     lds_barrier();
 }
-static_assert(kStage % kHistBlock == 0 && kStageBig % kHistBlock == 0 && kStageBig <= 65536,
-              "whole slots per thread; 16-bit order entries");
+static_assert(kStageBig <= 65536, "16-bit order entries");
 
 struct WalkState {
     AxisCross c[3];
@@ -653,10 +652,12 @@ __device__ __forceinline__ uint32_t euclid_moves(const StagedSeg& g, uint32_t N,
     return moves;
 }
 
-// Per-wave LDS of the Euclidean counts, one entry per lane: its segment's
-// first chunk number, length N and move count.
+// Per-wave LDS of the Euclidean counts, one entry per segment of a group: its
+// first chunk number, move count and length N (at most 16384).
+constexpr uint32_t kCountGroup = 32;
 struct CountScratch {
-    uint32_t pre[kWave], n[kWave], cnt[kWave];
+    uint32_t pre[kCountGroup], cnt[kCountGroup];
+    uint16_t n[kCountGroup];
 };
 constexpr size_t kCountScratch = (size_t)(kHistBlock / kWave) * sizeof(CountScratch);
 
@@ -668,7 +669,6 @@ constexpr size_t kCountScratch = (size_t)(kHistBlock / kWave) * sizeof(CountScra
 // at a time, one per lane, each lane finding its chunk's segment by binary
 // search over the prefix; a segment's moves are summed with LDS atomics.
 // counts: the stage's first segment's slot.
-constexpr uint32_t kCountGroup = 32;
 template <int kN>
 __device__ __forceinline__ void euclid_counts(const Stage<kN>& st, int32_t* __restrict__ counts,
                                               CountScratch* scratch) {
@@ -694,9 +694,11 @@ __device__ __forceinline__ void euclid_counts(const Stage<kN>& st, int32_t* __re
         const uint32_t ch = (N + kWave - 1) / kWave;
         const uint32_t incl = wave_inclusive_sum(ch);
         const uint32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
-        w.pre[lane] = incl - ch;
-        w.n[lane] = N;
-        w.cnt[lane] = 0u;
+        if (lane < kCountGroup) {
+            w.pre[lane] = incl - ch;
+            w.n[lane] = (uint16_t)N;
+            w.cnt[lane] = 0u;
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -706,7 +708,7 @@ __device__ __forceinline__ void euclid_counts(const Stage<kN>& st, int32_t* __re
                 // The last lane whose first chunk is at most q owns chunk q.
                 uint32_t o = 0;
 #pragma unroll
-                for (uint32_t step = kWave / 2; step > 0; step >>= 1) o += w.pre[o + step] <= q ? step : 0u;
+                for (uint32_t step = kCountGroup / 2; step > 0; step >>= 1) o += w.pre[o + step] <= q ? step : 0u;
                 const uint32_t n = w.n[o];
                 const uint32_t k0 = (q - w.pre[o]) * (uint32_t)kWave;
                 const uint32_t len = n - k0 < (uint32_t)kWave ? n - k0 : (uint32_t)kWave;
@@ -895,7 +897,7 @@ __device__ __forceinline__ void hist_row(const BrickScene& sc, uint32_t g, Stage
     for (uint32_t b = threadIdx.x; b < NB; b += kHistBlock) row[b] = lh[b];
 }
 
-// LDS of the histogram kernel: 8 192 staged segments and up to 8 192 brick
+// LDS of a plain call's histogram: 8 192 staged segments and up to 8 192 brick
 // counters, or 4 096 staged segments and up to 16 384 counters; each
 // workgroup takes the layout its scene's brick count allows.
 constexpr size_t kHistLdsBig = sizeof(Stage<kStageBig>) + (size_t)kBigStageBricks * 4;
@@ -904,23 +906,40 @@ constexpr size_t kHistLdsSmall = sizeof(Stage<kStage>) + (size_t)kMaxBricks * 4;
 constexpr size_t kHistLds = (kHistLdsBig > kHistLdsSmall ? kHistLdsBig : kHistLdsSmall) + kCountScratch;
 static_assert(kHistLds <= 163840, "histogram LDS fits a workgroup");
 
-__global__ __launch_bounds__(kHistBlock) void k_brick_hist(uint8_t* __restrict__ work) {
-    extern __shared__ __align__(16) uint8_t hist_lds[];
+// Batches have more rows than the chip has CUs, of about kSegsPerRow segments:
+// two workgroups a CU (80 KiB of LDS, 64 VGPRs each) hide each other's loads
+// and barriers, with room for every segment of a row beside the counters of
+// 4096 bricks, and for fewer at a time beside those of more.  256 scenes with
+// 9.6 M segments in all: 0.137 ms against 0.165 with one a CU; eight wireframes
+// 0.009 against 0.016.  (The scatter, of 94 VGPRs, gains nothing from two of
+// 512 threads, and loses more than half to the spills of two of 1024.)
+constexpr size_t kTwoPerCu = 81920;
+template <int kN>
+struct BatchLayout {
+    static constexpr uint32_t kBricks = kN == 4096 ? 4096u : (kN == 2048 ? 8192u : kMaxBricks);
+    static constexpr size_t kBytes = sizeof(Stage<kN>) + (size_t)kBricks * 4;
+    static_assert(kBytes <= kTwoPerCu - kCountScratch, "two workgroups a CU");
+    Stage<kN> st;
+    uint32_t bricks[kBricks];
+};
+static_assert(kSegsPerRow == 4096 && kMaxBricks == 16384, "layouts of the batch kernels");
+
+__global__ __launch_bounds__(kHistBlock, 8) void k_brick_hist(uint8_t* __restrict__ work) {
+    __shared__ __align__(16) uint8_t lds[kTwoPerCu];
     const TableView tv = table_view(work + kWorkTable);
     const WorkView wv = work_of(work, tv);
     const uint32_t r = xcd_row(blockIdx.x, gridDim.x);
     if (*wv.ok == 0 || r >= tv.h.rows) return;
     const BrickScene sc = tv.scenes[tv.row_scene ? tv.row_scene[r] : 0u];
     const uint32_t g = r - sc.row_base;
-    if (sc.bg.nbricks <= kBigStageBricks) {
-        auto* st = reinterpret_cast<Stage<kStageBig>*>(hist_lds);
-        hist_row(sc, g, *st, reinterpret_cast<uint32_t*>(hist_lds + sizeof(Stage<kStageBig>)),
-                 reinterpret_cast<CountScratch*>(hist_lds + kHistLdsBig), wv);
-    } else {
-        auto* st = reinterpret_cast<Stage<kStage>*>(hist_lds);
-        hist_row(sc, g, *st, reinterpret_cast<uint32_t*>(hist_lds + sizeof(Stage<kStage>)),
-                 reinterpret_cast<CountScratch*>(hist_lds + kHistLdsSmall), wv);
-    }
+    auto* scratch = reinterpret_cast<CountScratch*>(lds + kTwoPerCu - kCountScratch);
+    auto row = [&](auto* layout) { hist_row(sc, g, layout->st, layout->bricks, scratch, wv); };
+    if (sc.bg.nbricks <= BatchLayout<4096>::kBricks)
+        row(reinterpret_cast<BatchLayout<4096>*>(lds));
+    else if (sc.bg.nbricks <= BatchLayout<2048>::kBricks)
+        row(reinterpret_cast<BatchLayout<2048>*>(lds));
+    else
+        row(reinterpret_cast<BatchLayout<512>*>(lds));
 }
 
 // A plain call's plan and histogram in one launch: every workgroup plans the
@@ -2186,11 +2205,8 @@ hipError_t launch_bricks(const void* d_scenes, const void* one, const BrickLaunc
     hipError_t e;
     {
         static hipError_t attr = [] {
-            hipError_t r = hipFuncSetAttribute((const void*)k_brick_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)kHistLds);
-            if (r != hipSuccess) return r;
-            r = hipFuncSetAttribute((const void*)k_brick_plan_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)kHistLds);
+            hipError_t r = hipFuncSetAttribute((const void*)k_brick_plan_hist,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHistLds);
             if (r != hipSuccess) return r;
             return hipFuncSetAttribute((const void*)k_brick_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)(kMaxBricks * sizeof(uint32_t)));
@@ -2222,7 +2238,7 @@ hipError_t launch_bricks(const void* d_scenes, const void* one, const BrickLaunc
         }
         {
             KernelTimer t("brick_hist", stream);
-            k_brick_hist<<<L.rows, kHistBlock, kHistLds, stream>>>(work);
+            k_brick_hist<<<L.rows, kHistBlock, 0, stream>>>(work);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

@@ -53,3 +53,21 @@ def test_near_brick_faces(dims, lg, n, euclid, want_counts):
     if want_counts:
         got = to_host(counts)[segs[:, 4] < dims[1]]
         assert np.array_equal(got, (oracle.counts_euclid if euclid else oracle.counts)(inside))
+
+
+@pytest.mark.parametrize("dims", [(1024, 2048, 1024), (1024, 2048, 1056), (2048, 2048, 1024), (2048, 2080, 1056)])
+@pytest.mark.parametrize("euclid", [False, True])
+def test_batch_with_many_bricks(dims, euclid):
+    """4096 bricks in a scene and more, 8192 and more, beside a small scene."""
+    import torch
+    from tests.test_gpu_batch import Batch, run_batch
+    flags = binding.VOX_GRID_CLEAR | (binding.VOX_GRID_EUCLID if euclid else 0)
+    specs = []
+    for d, n in ((dims, 9001), ((128, 100, 90), 5000)):
+        segs = near_faces(d, (8, 6, 5), n, sum(d))
+        specs.append((segs[segs[:, 4] < d[1]], d, flags, None, True))
+    b = Batch(specs)
+    status, _ = run_batch(b, tuning=binding.make_tuning((8, 6, 5)))
+    assert status == binding.VOX_OK
+    b.check()
+    torch.cuda.empty_cache()
