@@ -1737,7 +1737,7 @@ struct RoundQueue {
 // 0.61 -> 0.50 ms, VALU wave instructions 227 -> 160 M; 100 000 into 512^3
 // 19.8 -> 17.5 us.
 template <int LGX, int LGY, int LGZ, int kWgs>
-__global__ __launch_bounds__((FillCfg<LGX, LGY, LGZ, kWgs>::kBlock), kWgs)
+__global__ __launch_bounds__((FillCfg<LGX, LGY, LGZ, kWgs>::kBlock), 4)  // 16 waves a CU
 void k_brick_fill(uint8_t* __restrict__ work) {
     using Shape = BrickShape<LGX, LGY, LGZ>;
     using Cfg = FillCfg<LGX, LGY, LGZ, kWgs>;
