@@ -28,15 +28,17 @@
 //   colscan   per brick, exclusive prefix of the rows over workgroups, and
 //             the brick's piece total
 //   base      exclusive scan of the brick totals -> bin offsets; if the
-//             records do not fit the workspace, the direct kernels take over;
+//             records do not fit the workspace, the direct kernel takes over;
 //             the fill's work items: one per brick, several for a brick with
 //             more than a fair share of the records
-//   clear     (batches) zeroes the volumes of the cleared direct scenes
+//             (a plain call of few bricks and rows: colscan and base are done
+//             inside the scatter)
 //   scatter   zeroes the bricks cut into several items in cleared volumes,
 //             then the same walk again, writing one 16-byte piece record
 //             (start point, direction, k-window in the brick) into the
 //             brick's bin
-//   fill      persistent workgroups take work items from work-stealing
+//   fill      zeroes the volumes of the cleared direct scenes (batches);
+//             persistent workgroups take work items from work-stealing
 //             queues, set the bits of every piece with LDS atomic OR and
 //             flush the brick to the volume (an item that holds part of a
 //             brick with device atomic OR)
@@ -1293,6 +1295,30 @@ struct PieceMakerEuclid {
     }
 };
 
+// Zeroes brick lb of a scene in its volume (a workgroup).
+__device__ __forceinline__ void zero_brick(const BrickScene& sc, uint32_t lb) {
+    const BrickGeom& bg = sc.bg;
+    const int32_t org[3] = {(int32_t)(lb % (uint32_t)bg.nb[0]) << bg.lg[0],
+                            (int32_t)((lb / (uint32_t)bg.nb[0]) % (uint32_t)bg.nb[1]) << bg.lg[1],
+                            (int32_t)(lb / ((uint32_t)bg.nb[0] * (uint32_t)bg.nb[1])) << bg.lg[2]};
+    int32_t ext[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        const int32_t e = bg.dim[ax] - org[ax];
+        ext[ax] = e < (1 << bg.lg[ax]) ? e : (1 << bg.lg[ax]);
+    }
+    // A brick has at most 2^20 bits: 32-bit index arithmetic.
+    const uint32_t xws = (uint32_t)ext[0] >> 5, ey = (uint32_t)ext[1];
+    const uint32_t words = xws * ey * (uint32_t)ext[2];
+    const int64_t row_words = (int64_t)bg.dim[0] >> 5;
+    for (uint32_t t = threadIdx.x; t < words; t += blockDim.x) {
+        const uint32_t xw = t % xws, r = t / xws;
+        const uint32_t y = r % ey, z = r / ey;
+        sc.grid[((int64_t)(org[2] + (int32_t)z) * bg.dim[1] + (org[1] + (int32_t)y)) * row_words + (org[0] >> 5) +
+                xw] = 0u;
+    }
+}
+
 // In cleared brick scenes, zeroes the bricks cut into several work items
 // (their items OR into the volume), one workgroup a brick, before the fill.
 __device__ __forceinline__ void zero_cut_bricks(const TableView& tv, const WorkView& wv) {
@@ -1300,47 +1326,117 @@ __device__ __forceinline__ void zero_cut_bricks(const TableView& tv, const WorkV
     for (uint32_t j = blockIdx.x; j < ns; j += gridDim.x) {
         const uint32_t gb = wv.split[j];
         const BrickScene& sc = tv.scenes[tv.brick_scene ? tv.brick_scene[gb] : 0u];
-        if (!(sc.flags & kSceneClear)) continue;
-        const BrickGeom& bg = sc.bg;
-        const uint32_t lb = gb - sc.brick_base;
-        const int32_t org[3] = {(int32_t)(lb % (uint32_t)bg.nb[0]) << bg.lg[0],
-                                (int32_t)((lb / (uint32_t)bg.nb[0]) % (uint32_t)bg.nb[1]) << bg.lg[1],
-                                (int32_t)(lb / ((uint32_t)bg.nb[0] * (uint32_t)bg.nb[1])) << bg.lg[2]};
-        int32_t ext[3];
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const int32_t e = bg.dim[ax] - org[ax];
-            ext[ax] = e < (1 << bg.lg[ax]) ? e : (1 << bg.lg[ax]);
-        }
-        // A brick has at most 2^20 bits: 32-bit index arithmetic.
-        const uint32_t xws = (uint32_t)ext[0] >> 5, ey = (uint32_t)ext[1];
-        const uint32_t words = xws * ey * (uint32_t)ext[2];
-        const int64_t row_words = (int64_t)bg.dim[0] >> 5;
-        for (uint32_t t = threadIdx.x; t < words; t += blockDim.x) {
-            const uint32_t xw = t % xws, r = t / xws;
-            const uint32_t y = r % ey, z = r / ey;
-            sc.grid[((int64_t)(org[2] + (int32_t)z) * bg.dim[1] + (org[1] + (int32_t)y)) * row_words +
-                    (org[0] >> 5) + xw] = 0u;
-        }
+        if (sc.flags & kSceneClear) zero_brick(sc, gb - sc.brick_base);
     }
 }
 
-__global__ __launch_bounds__(kHistBlock) void k_brick_scatter(uint8_t* __restrict__ work) {
+// The colscan and base kernels' work for a plain call of few bricks and rows,
+// by every workgroup of the scatter for itself: this row's bin offsets from
+// the histogram (all of it is read), the cut bricks zeroed, and by workgroup 0
+// the words that the fill reads.  False: the records do not fit.
+//
+// Two launches of latency (5 to 7 us each) for the reading of rows x bricks
+// words by every workgroup.  Measured per call with against without, by words:
+// 1 M segments in 256^3 (8 K) 79.8 / 89.7 us, 20 000 in 512^3 (10 K) 37.6 / 42.2,
+// 100 000 in 512^3 (50 K) 43.3 / 45.6, 300 000 (64 K) 61.4 / 64.8; 100 000 in
+// 768^3 (169 K) 90 / 79.
+constexpr uint32_t kScanBricks = kHistBlock;    // a thread per brick
+constexpr uint32_t kScanWords = 65536;
+__device__ __forceinline__ bool scan_in_scatter(const BrickScene& sc, const WorkView& wv, uint32_t g,
+                                                uint64_t work_bytes, uint32_t* cur) {
+    __shared__ uint32_t tot[kScanBricks];
+    __shared__ uint64_t lds[kHistBlock / kWave];
+    __shared__ uint32_t max_s;
+    const uint32_t NB = sc.bg.nbricks, G = sc.rows, t = threadIdx.x;
+    if (t < NB) tot[t] = cur[t] = 0u;
+    if (t == 0) max_s = 0u;
+    lds_barrier();
+    // Rows c, c + parts, ... of bricks [b, b + per).
+    auto sums = [&](auto kPer) {
+        constexpr uint32_t per = decltype(kPer)::value;
+        typedef uint32_t Words __attribute__((ext_vector_type(per)));
+        const uint32_t units = NB / per, parts = (uint32_t)kHistBlock / units, b = t % units, c = t / units;
+        if (c >= parts) return;
+        const Words* col = reinterpret_cast<const Words*>(wv.hist) + b;
+        Words sum = {}, before = {};
+#pragma unroll 8
+        for (uint32_t r = c; r < G; r += parts) {
+            const Words v = col[(size_t)r * units];
+            sum += v;
+            before += r < g ? v : (Words){};
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < per; ++i) {
+            atomicAdd(&tot[per * b + i], sum[i]);
+            atomicAdd(&cur[per * b + i], before[i]);
+        }
+    };
+    if (NB % 4u == 0u)
+        sums(std::integral_constant<uint32_t, 4>{});
+    else
+        sums(std::integral_constant<uint32_t, 1>{});
+    lds_barrier();
+    const uint32_t mine = t < NB ? tot[t] : 0u;
+    atomicMax(&max_s, mine);
+    uint64_t total;
+    const uint64_t base = block_exclusive_sum<kHistBlock>((uint64_t)mine, lds, total);
+    if (t < NB) cur[t] += (uint32_t)base;
+    const uint64_t cap = work_bytes > wv.rec_off ? (work_bytes - wv.rec_off) / sizeof(Piece) : 0u;
+    const bool fits = total <= cap && total < 0xFFFFFFFFull;
+    const uint64_t T = split_threshold(total);
+    const bool cut = (uint64_t)max_s > T;  // (complete: the sum has barriers)
+    if (cut && fits && (sc.flags & kSceneClear))
+        for (uint32_t i = blockIdx.x; i < NB; i += gridDim.x)
+            if ((uint64_t)tot[i] > T) zero_brick(sc, i);
+    if (blockIdx.x == 0) {
+        // Extra items, and above them the cut bricks.
+        const uint32_t more = t < NB ? brick_items(mine, T) - 1u : 0u;
+        uint64_t extra = 0, first = 0;
+        if (cut) first = block_exclusive_sum<kHistBlock>((more ? uint64_t(1) << 32 : 0u) | more, lds, extra);
+        if (t < NB) {
+            wv.bin_base[t] = (uint32_t)base;
+            if (cut) {
+                wv.item_base[t] = (uint32_t)first;
+                for (uint32_t j = 0; j < more && fits; ++j) wv.item_brick[(uint32_t)first + j] = t;
+            }
+        }
+        if (t == 0) {
+            wv.bin_base[NB] = (uint32_t)total;
+            *wv.pieces = total;
+            if (!fits) *wv.direct_all = 1u;
+            if (cut) wv.item_base[NB] = (uint32_t)extra;
+            *wv.n_items = cut ? (((uint32_t)extra + 1u) & ~1u) + NB : NB;
+            *wv.n_split = (uint32_t)(extra >> 32);
+        }
+    }
+    return fits;
+}
+
+template <bool kScan>
+__global__ __launch_bounds__(kHistBlock) void k_brick_scatter(uint8_t* __restrict__ work, uint64_t work_bytes) {
     extern __shared__ uint32_t cur[];
     __shared__ Stage<kStage> st;
     const TableView tv = table_view(work + kWorkTable);
     const WorkView wv = work_of(work, tv);
     const uint32_t r = xcd_row(blockIdx.x, gridDim.x);
-    if (*wv.ok == 0 || *wv.direct_all != 0) return;
-    zero_cut_bricks(tv, wv);
-    if (r >= tv.h.rows) return;
-    const BrickScene sc = tv.scenes[tv.row_scene ? tv.row_scene[r] : 0u];
+    if (*wv.ok == 0) return;
+    if constexpr (!kScan) {
+        if (*wv.direct_all != 0) return;
+        zero_cut_bricks(tv, wv);
+        if (r >= tv.h.rows) return;
+    }
+    const BrickScene sc = tv.scenes[!kScan && tv.row_scene ? tv.row_scene[r] : 0u];
     const BrickGeom& bg = sc.bg;
     const uint32_t NB = bg.nbricks;
     const uint32_t g = r - sc.row_base;
-    const uint32_t* row = wv.hist + sc.hist_off + (size_t)g * NB;
-    const uint32_t* base_b = wv.bin_base + sc.brick_base;
-    for (uint32_t b = threadIdx.x; b < NB; b += kHistBlock) cur[b] = base_b[b] + row[b];
+    if constexpr (kScan) {
+        // (As many workgroups as rows.)
+        if (!scan_in_scatter(sc, wv, r, work_bytes, cur) || r >= tv.h.rows) return;
+    } else {
+        const uint32_t* row = wv.hist + sc.hist_off + (size_t)g * NB;
+        const uint32_t* base_b = wv.bin_base + sc.brick_base;
+        for (uint32_t b = threadIdx.x; b < NB; b += kHistBlock) cur[b] = base_b[b] + row[b];
+    }
     int64_t lo, hi;
     seg_range(sc.n, (int)g, (int)sc.rows, lo, hi);
     Piece* __restrict__ recs = wv.recs;
@@ -1554,6 +1650,34 @@ __device__ __forceinline__ u32x4 swap_rows(const u32x4& v) {
                    (uint32_t)__builtin_amdgcn_mov_dpp((int)w, kPerm, 0xf, 0xf, true)};
 }
 
+// The scenes the direct kernel serves: those the brick path does not take
+// (flagged by the plan), or every scene when the records did not fit.
+// Nothing runs after a failed plan.
+__device__ __forceinline__ bool direct_scenes(const uint8_t* work, const TableView& tv, uint32_t& count,
+                                              bool& all) {
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(work);
+    if (w[kWStatus] & (uint32_t)(kStatusInvalid | kStatusLaunch)) return false;
+    all = w[kWDirectAll] != 0;
+    count = all ? tv.h.n_scenes : tv.h.n_direct;
+    return count > 0;
+}
+
+// Zeroes the volumes of the cleared direct scenes (whose bits the direct kernel
+// sets after the fill).
+__device__ __forceinline__ void clear_direct_scenes(const uint8_t* work, const TableView& tv) {
+    uint32_t nd;
+    bool all;
+    if (!direct_scenes(work, tv, nd, all)) return;
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t ts = (int64_t)gridDim.x * blockDim.x;
+    for (uint32_t j = 0; j < nd; ++j) {
+        const BrickScene& sc = tv.scenes[all ? j : tv.direct[j]];
+        if (!(sc.flags & kSceneClear)) continue;
+        const int64_t nwords = ((int64_t)sc.bg.dim[0] * sc.bg.dim[1] * sc.bg.dim[2] + 31) / 32;
+        clear_words(sc.grid, nwords, t0, ts);
+    }
+}
+
 // Launch shape of the fill kernel: kWgs workgroups per CU, of 1024 threads
 // (one per CU) or 512 (two per CU).  A 128 KiB brick takes a whole CU; 64 KiB
 // bricks run either way: two workgroups per CU, so that one workgroup's brick
@@ -1754,6 +1878,7 @@ void k_brick_fill(uint8_t* __restrict__ work) {
 
     const TableView tv = table_view(work + kWorkTable);
     const WorkView wv = work_of(work, tv);
+    if (*wv.direct_all != 0 || tv.h.n_direct != 0) clear_direct_scenes(work, tv);
     if (*wv.ok == 0 || *wv.direct_all != 0) return;
     const uint32_t NB = tv.h.bricks;  // global bricks of all scenes
     FillQueue q;
@@ -1771,7 +1896,6 @@ void k_brick_fill(uint8_t* __restrict__ work) {
     q.xcd = blockIdx.x % (uint32_t)kXcds;
     q.wgs = gridDim.x;
     uint32_t second = q.items;
-    const uint32_t lane = __lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const u32x4* recv = reinterpret_cast<const u32x4*>(wv.recs);
     const uint32_t* recw = reinterpret_cast<const uint32_t*>(wv.recs);
@@ -2030,35 +2154,6 @@ void k_brick_fill(uint8_t* __restrict__ work) {
 
 constexpr int kDirectBlock = 256;
 
-// The scenes the direct kernels serve: those the brick path does not take
-// (flagged by the plan), or every scene when the records did not fit.
-// Nothing runs after a failed plan.
-__device__ __forceinline__ bool direct_scenes(const uint8_t* work, const TableView& tv, uint32_t& count,
-                                              bool& all) {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(work);
-    if (w[kWStatus] & (uint32_t)(kStatusInvalid | kStatusLaunch)) return false;
-    all = w[kWDirectAll] != 0;
-    count = all ? tv.h.n_scenes : tv.h.n_direct;
-    return count > 0;
-}
-
-// Zeroes the volumes of the cleared direct scenes (before the fill; the
-// direct kernel sets their bits after it).
-__global__ __launch_bounds__(kDirectBlock) void k_batch_direct_clear(uint8_t* __restrict__ work) {
-    const TableView tv = table_view(work + kWorkTable);
-    const int64_t t0 = (int64_t)blockIdx.x * kDirectBlock + threadIdx.x;
-    const int64_t ts = (int64_t)gridDim.x * kDirectBlock;
-    uint32_t nd;
-    bool all;
-    if (!direct_scenes(work, tv, nd, all)) return;
-    for (uint32_t j = 0; j < nd; ++j) {
-        const BrickScene& sc = tv.scenes[all ? j : tv.direct[j]];
-        if (!(sc.flags & kSceneClear)) continue;
-        const int64_t nwords = ((int64_t)sc.bg.dim[0] * sc.bg.dim[1] * sc.bg.dim[2] + 31) / 32;
-        clear_words(sc.grid, nwords, t0, ts);
-    }
-}
-
 // The segments of the direct scenes, one device atomic per voxel
 // (direct_segments, vox_direct.h).
 __global__ __launch_bounds__(kDirectBlock) void k_batch_direct(uint8_t* __restrict__ work) {
@@ -2208,14 +2303,14 @@ hipError_t launch_bricks(const void* d_scenes, const void* one, const BrickLaunc
             hipError_t r = hipFuncSetAttribute((const void*)k_brick_plan_hist,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHistLds);
             if (r != hipSuccess) return r;
-            return hipFuncSetAttribute((const void*)k_brick_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
+            return hipFuncSetAttribute((const void*)k_brick_scatter<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)(kMaxBricks * sizeof(uint32_t)));
         }();
         if (attr != hipSuccess) return attr;
     }
     // A plain call (its one scene by value; the brick geometry keeps it to at
-    // most kMaxBricks bricks): the plan runs inside the histogram launch,
-    // five launches in all; a batch (a device scene array) takes seven or
+    // most kMaxBricks bricks): the plan runs inside the histogram launch, three
+    // to five launches in all; a batch (a device scene array) takes seven or
     // more.
     if (one) {
         if (L.n_scenes != 1 || L.bricks > kMaxBricks) return hipErrorInvalidValue;
@@ -2242,27 +2337,33 @@ hipError_t launch_bricks(const void* d_scenes, const void* one, const BrickLaunc
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    {
-        KernelTimer t("brick_colscan", stream);
-        uint32_t blocks = (L.bricks + kColBins - 1) / kColBins;
-        if (blocks > kColMaxBlocks) blocks = kColMaxBlocks;
-        k_brick_colscan<<<blocks, 256, 0, stream>>>(work);
+    // A plain call with few histogram words scans them in the scatter.
+    BrickScene plan{};
+    if (one) (void)plan_scene(*static_cast<const vox_scene*>(one), L.lg, (int64_t)L.segs_per_row, plan);
+    const uint32_t nb = plan.bg.nbricks;
+    const bool scan = nb != 0u && nb <= kScanBricks && nb * plan.rows <= kScanWords;
+    if (!scan) {
+        {
+            KernelTimer t("brick_colscan", stream);
+            uint32_t blocks = (L.bricks + kColBins - 1) / kColBins;
+            if (blocks > kColMaxBlocks) blocks = kColMaxBlocks;
+            k_brick_colscan<<<blocks, 256, 0, stream>>>(work);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        {
+            KernelTimer t("brick_base", stream);
+            k_brick_base<<<1, kBaseBlock, 0, stream>>>(work, (uint64_t)work_bytes);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    {
-        KernelTimer t("brick_base", stream);
-        k_brick_base<<<1, kBaseBlock, 0, stream>>>(work, (uint64_t)work_bytes);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (L.direct_kernels) {
-        KernelTimer t("batch_direct_clear", stream);
-        k_batch_direct_clear<<<2048, kDirectBlock, 0, stream>>>(work);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     {
         KernelTimer t("brick_scatter", stream);
-        const size_t scatter_lds = (size_t)(L.n_scenes > 1 ? kMaxBricks : L.bricks) * sizeof(uint32_t);
-        k_brick_scatter<<<L.rows, kHistBlock, scatter_lds, stream>>>(work);
+        const uint32_t counters = scan ? nb : (L.n_scenes > 1 ? kMaxBricks : L.bricks);
+        const size_t scatter_lds = (size_t)counters * sizeof(uint32_t);
+        if (scan)
+            k_brick_scatter<true><<<L.rows, kHistBlock, scatter_lds, stream>>>(work, (uint64_t)work_bytes);
+        else
+            k_brick_scatter<false><<<L.rows, kHistBlock, scatter_lds, stream>>>(work, (uint64_t)work_bytes);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     {
@@ -2277,7 +2378,7 @@ hipError_t launch_bricks(const void* d_scenes, const void* one, const BrickLaunc
     if (e != hipSuccess) return e;
     if (L.direct_kernels) {
         KernelTimer t("batch_direct", stream);
-        k_batch_direct<<<4096, kDirectBlock, 0, stream>>>(work);
+        k_batch_direct<<<2048, kDirectBlock, 0, stream>>>(work);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
