@@ -2,6 +2,7 @@
 // carving and the launch sequence of each call.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -117,6 +118,154 @@ bool tuning_cache_lookup(int32_t dx, int32_t dy, int32_t dz, int64_t n, Tuning& 
 
 }  // namespace vox
 
+namespace {
+
+// Pinned host memory in which a call finds its status and total after the
+// synchronisation, written by the kernel that computes them: a copy from the
+// workspace costs 10 us more.  One page for the process, allocated by the first
+// call that asks for a total; a call takes a slot of its own for as long as it
+// lasts, and copies when none is free.
+class HostSlots {
+  public:
+    struct Slot {
+        int64_t status, total, pad[6];
+    };
+    Slot* take(bool may_allocate) {
+        Slot* page = page_.load(std::memory_order_acquire);
+        if (page == nullptr && may_allocate) page = allocate();
+        if (page == nullptr) return nullptr;
+        uint64_t used = used_.load(std::memory_order_relaxed);
+        while (used != ~uint64_t(0)) {
+            const int i = __builtin_ctzll(~used);
+            if (used_.compare_exchange_weak(used, used | uint64_t(1) << i, std::memory_order_acquire)) return page + i;
+        }
+        return nullptr;
+    }
+    void give_back(Slot* s) {
+        used_.fetch_and(~(uint64_t(1) << (s - page_.load(std::memory_order_relaxed))), std::memory_order_release);
+    }
+
+  private:
+    Slot* allocate() {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (tried_) return page_.load(std::memory_order_relaxed);
+        tried_ = true;
+        // (Another thread may be capturing a graph: not a part of it.)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+        void* p = nullptr;
+        const hipError_t e = hipHostMalloc(&p, 64 * sizeof(Slot), hipHostMallocPortable | hipHostMallocMapped);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        page_.store(static_cast<Slot*>(p), std::memory_order_release);
+        return static_cast<Slot*>(p);
+    }
+    std::atomic<Slot*> page_{nullptr};
+    std::atomic<uint64_t> used_{0};
+    std::mutex mu_;
+    bool tried_ = false;
+};
+HostSlots g_slots;
+
+}  // namespace
+
+int vox::segments_to_list(const void* d_segs, int64_t n, int64_t* d_offsets, void* d_voxels, int64_t capacity,
+                          int64_t* h_total, void* d_work, size_t work_bytes, void* stream, int kind,
+                          bool may_allocate) {
+    const bool euclid = kind == kListEuclid;
+    if (n < 0) return fail(VOX_ERR_INVALID_ARGUMENT, "n must be >= 0");
+    if (n > (int64_t(1) << 31) - 2) return fail(VOX_ERR_INVALID_ARGUMENT, "n must be < 2^31 - 1");
+    if (n > 0 && d_segs == nullptr) return fail(VOX_ERR_INVALID_ARGUMENT, "d_segs is NULL");
+    if (d_segs && !aligned(d_segs, 4)) return fail(VOX_ERR_INVALID_ARGUMENT, "d_segs not 4-byte aligned");
+    if (d_offsets == nullptr || !aligned(d_offsets, 8))
+        return fail(VOX_ERR_INVALID_ARGUMENT, "d_offsets NULL or not 8-byte aligned");
+    if (capacity < 0) return fail(VOX_ERR_INVALID_ARGUMENT, "capacity must be >= 0");
+    if (d_voxels && !aligned(d_voxels, 16))
+        return fail(VOX_ERR_INVALID_ARGUMENT, "d_voxels not 16-byte aligned");
+    const bool want = d_voxels != nullptr && capacity > 0;
+    const int64_t cap = want ? capacity : 0;
+    if (d_work == nullptr || !aligned(d_work, vox::kAlign))
+        return fail(VOX_ERR_WORKSPACE, "d_work NULL or not 256-byte aligned");
+    const size_t need = vox::list_workspace_bytes(n, cap);
+    if (work_bytes < need)
+        return fail(VOX_ERR_WORKSPACE, "workspace %zu bytes, need %zu", work_bytes, need);
+
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int32_t* segs = reinterpret_cast<const int32_t*>(d_segs);
+    const bool a8 = aligned(d_segs, 8);
+    vox::ListWork w = vox::list_workspace(d_work, n, cap);
+    hipError_t e;
+    HostSlots::Slot* slot = h_total ? g_slots.take(may_allocate) : nullptr;
+    void* mapped = nullptr;
+    if (slot && hipHostGetDevicePointer(&mapped, slot, 0) != hipSuccess) {
+        g_slots.give_back(slot);
+        slot = nullptr;
+    }
+    w.host = static_cast<int64_t*>(mapped);
+    const bool at_once = want && !euclid && vox::list_one_launch(n, cap);
+    if (at_once) {
+        // (The kernel itself checks the header before it writes a voxel.)
+        if ((e = vox::launch_list_all(segs, n, a8, d_offsets, w, d_voxels, cap, s, (vox::ListKind)kind)) != hipSuccess)
+            return device_fail(e, "voxels");
+    } else if (n >= 1 && n <= vox::kSegsPerCountBlock) {
+        // One block counts, scans and places.
+        if ((e = vox::launch_list_one_block(segs, n, a8, w, d_offsets, cap, s, (vox::ListKind)kind)) != hipSuccess)
+            return device_fail(e, "count");
+    } else {
+        if ((e = vox::launch_list_count(segs, n, a8, w, s, (vox::ListKind)kind)) != hipSuccess)
+            return device_fail(e, "count");
+        if ((e = vox::launch_list_scan(w, n, d_offsets, cap, s)) != hipSuccess)
+            return device_fail(e, "scan");
+        // (The Euclidean lists are written per segment: no output tiles.)
+        if ((e = vox::launch_list_offsets(n, d_offsets, w, cap, want && !euclid, s)) != hipSuccess)
+            return device_fail(e, "offsets");
+    }
+
+    int64_t tiles = want ? (cap + vox::kListTile - 1) / vox::kListTile : 0;
+    vox_status result = VOX_OK;
+    if (h_total) {
+        // One synchronisation: learn the total (and the status) before the
+        // voxel launch so it can be sized exactly.
+        int64_t hdr[2];
+        if (!slot && (e = hipMemcpyAsync(hdr, d_work, sizeof(hdr), hipMemcpyDeviceToHost, s)) != hipSuccess)
+            return device_fail(e, "read total");
+        // (After an error the slot stays taken: a kernel may still write it.)
+        if ((e = hipStreamSynchronize(s)) != hipSuccess) return device_fail(e, "synchronize");
+        if (slot) {
+            hdr[0] = __atomic_load_n(&slot->status, __ATOMIC_RELAXED);
+            hdr[1] = __atomic_load_n(&slot->total, __ATOMIC_RELAXED);
+            g_slots.give_back(slot);
+        }
+        const int32_t st = (int32_t)(hdr[0] & 0xFFFFFFFF);
+        *h_total = hdr[1];
+        if (st & vox::kStatusOutOfRange) {
+            result = kind == vox::kListI32
+                         ? fail(VOX_ERR_OUT_OF_RANGE, "a segment spans 2^30 or more voxels along an axis")
+                         : fail(VOX_ERR_OUT_OF_RANGE, "a segment end point lies outside the int16 range");
+            tiles = 0;
+        } else if (st & vox::kStatusCapacity) {
+            result = fail(VOX_ERR_CAPACITY, "total %lld voxels exceeds capacity %lld",
+                          (long long)hdr[1], (long long)capacity);
+            tiles = 0;
+        } else {
+            tiles = want ? (hdr[1] + vox::kListTile - 1) / vox::kListTile : 0;
+        }
+    }
+    if (tiles > 0 && !at_once) {
+        if (euclid)
+            e = vox::launch_list_voxels_euclid(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), s);
+        else if (kind == vox::kListI32)
+            e = vox::launch_list_voxels32(segs, n, a8, d_offsets, w, static_cast<int32_t*>(d_voxels), tiles, s);
+        else
+            e = vox::launch_list_voxels(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), tiles, s);
+        if (e != hipSuccess) return device_fail(e, "voxels");
+    }
+    return result == VOX_OK ? ok() : result;
+}
+
 extern "C" {
 
 vox_status vox_tuning_cache_set(int32_t dim_x, int32_t dim_y, int32_t dim_z, int64_t n_segments,
@@ -183,105 +332,25 @@ size_t vox_list_workspace_bytes(int64_t n, int64_t capacity) {
     return vox::list_workspace_bytes(n, capacity);
 }
 
-static vox_status segments_to_list(const vox_segment* d_segs, int64_t n, int64_t* d_offsets,
-                                   void* d_voxels, int64_t capacity, int64_t* h_total,
-                                   void* d_work, size_t work_bytes, void* stream, vox::ListKind kind) {
-    const bool euclid = kind == vox::kListEuclid;
-    if (n < 0) return fail(VOX_ERR_INVALID_ARGUMENT, "n must be >= 0");
-    if (n > (int64_t(1) << 31) - 2) return fail(VOX_ERR_INVALID_ARGUMENT, "n must be < 2^31 - 1");
-    if (n > 0 && d_segs == nullptr) return fail(VOX_ERR_INVALID_ARGUMENT, "d_segs is NULL");
-    if (d_segs && !aligned(d_segs, 4)) return fail(VOX_ERR_INVALID_ARGUMENT, "d_segs not 4-byte aligned");
-    if (d_offsets == nullptr || !aligned(d_offsets, 8))
-        return fail(VOX_ERR_INVALID_ARGUMENT, "d_offsets NULL or not 8-byte aligned");
-    if (capacity < 0) return fail(VOX_ERR_INVALID_ARGUMENT, "capacity must be >= 0");
-    if (d_voxels && !aligned(d_voxels, 16))
-        return fail(VOX_ERR_INVALID_ARGUMENT, "d_voxels not 16-byte aligned");
-    const bool want = d_voxels != nullptr && capacity > 0;
-    const int64_t cap = want ? capacity : 0;
-    if (d_work == nullptr || !aligned(d_work, vox::kAlign))
-        return fail(VOX_ERR_WORKSPACE, "d_work NULL or not 256-byte aligned");
-    const size_t need = vox::list_workspace_bytes(n, cap);
-    if (work_bytes < need)
-        return fail(VOX_ERR_WORKSPACE, "workspace %zu bytes, need %zu", work_bytes, need);
-
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const int32_t* segs = reinterpret_cast<const int32_t*>(d_segs);
-    const bool a8 = aligned(d_segs, 8);
-    vox::ListWork w = vox::list_workspace(d_work, n, cap);
-    hipError_t e;
-    const bool at_once = want && !euclid && vox::list_one_launch(n, cap);
-    if (at_once) {
-        // (The kernel itself checks the header before it writes a voxel.)
-        if ((e = vox::launch_list_all(segs, n, a8, d_offsets, w, d_voxels, cap, s, kind)) != hipSuccess)
-            return device_fail(e, "voxels");
-    } else if (n >= 1 && n <= vox::kSegsPerCountBlock) {
-        // One block counts, scans and places.
-        if ((e = vox::launch_list_one_block(segs, n, a8, w, d_offsets, cap, s, kind)) != hipSuccess)
-            return device_fail(e, "count");
-    } else {
-        if ((e = vox::launch_list_count(segs, n, a8, w, s, kind)) != hipSuccess) return device_fail(e, "count");
-        if ((e = vox::launch_list_scan(w, n, d_offsets, cap, s)) != hipSuccess)
-            return device_fail(e, "scan");
-        // (The Euclidean lists are written per segment: no output tiles.)
-        if ((e = vox::launch_list_offsets(n, d_offsets, w, cap, want && !euclid, s)) != hipSuccess)
-            return device_fail(e, "offsets");
-    }
-
-    int64_t tiles = want ? (cap + vox::kListTile - 1) / vox::kListTile : 0;
-    vox_status result = VOX_OK;
-    if (h_total) {
-        // One synchronisation: learn the total (and the status) before the
-        // voxel launch so it can be sized exactly.
-        int64_t hdr[2];
-        if ((e = hipMemcpyAsync(hdr, d_work, sizeof(hdr), hipMemcpyDeviceToHost, s)) != hipSuccess)
-            return device_fail(e, "read total");
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return device_fail(e, "synchronize");
-        const int32_t st = (int32_t)(hdr[0] & 0xFFFFFFFF);
-        *h_total = hdr[1];
-        if (st & vox::kStatusOutOfRange) {
-            result = kind == vox::kListI32
-                         ? fail(VOX_ERR_OUT_OF_RANGE, "a segment spans 2^30 or more voxels along an axis")
-                         : fail(VOX_ERR_OUT_OF_RANGE, "a segment end point lies outside the int16 range");
-            tiles = 0;
-        } else if (st & vox::kStatusCapacity) {
-            result = fail(VOX_ERR_CAPACITY, "total %lld voxels exceeds capacity %lld",
-                          (long long)hdr[1], (long long)capacity);
-            tiles = 0;
-        } else {
-            tiles = want ? (hdr[1] + vox::kListTile - 1) / vox::kListTile : 0;
-        }
-    }
-    if (tiles > 0 && !at_once) {
-        if (euclid)
-            e = vox::launch_list_voxels_euclid(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), s);
-        else if (kind == vox::kListI32)
-            e = vox::launch_list_voxels32(segs, n, a8, d_offsets, w, static_cast<int32_t*>(d_voxels), tiles, s);
-        else
-            e = vox::launch_list_voxels(segs, n, a8, d_offsets, w, static_cast<int16_t*>(d_voxels), tiles, s);
-        if (e != hipSuccess) return device_fail(e, "voxels");
-    }
-    return result == VOX_OK ? ok() : result;
-}
-
 vox_status vox_segments_to_list(const vox_segment* d_segs, int64_t n, int64_t* d_offsets,
                                 int16_t* d_voxels, int64_t capacity, int64_t* h_total,
                                 void* d_work, size_t work_bytes, void* stream) {
-    return segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, d_work, work_bytes, stream,
-                            vox::kListI16);
+    return (vox_status)vox::segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, d_work, work_bytes,
+                                             stream, vox::kListI16, true);
 }
 
 vox_status vox_segments_to_list32(const vox_segment* d_segs, int64_t n, int64_t* d_offsets,
                                   int32_t* d_voxels, int64_t capacity, int64_t* h_total,
                                   void* d_work, size_t work_bytes, void* stream) {
-    return segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, d_work, work_bytes, stream,
-                            vox::kListI32);
+    return (vox_status)vox::segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, d_work, work_bytes,
+                                             stream, vox::kListI32, true);
 }
 
 vox_status vox_segments_to_list_euclid(const vox_segment* d_segs, int64_t n, int64_t* d_offsets,
                                        int16_t* d_voxels, int64_t capacity, int64_t* h_total,
                                        void* d_work, size_t work_bytes, void* stream) {
-    return segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, d_work, work_bytes, stream,
-                            vox::kListEuclid);
+    return (vox_status)vox::segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, d_work, work_bytes,
+                                             stream, vox::kListEuclid, true);
 }
 
 size_t vox_grid_workspace_bytes(int64_t n, int32_t dim_x, int32_t dim_y, int32_t dim_z) {

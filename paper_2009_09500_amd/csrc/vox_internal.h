@@ -58,7 +58,13 @@ struct ListWork {
     int32_t* tile_seg;     // [ntiles + 1]
     int64_t nb;
     int64_t ntiles;
+    int64_t* host = nullptr;  // host memory that also gets the status word and the total, or null
 };
+
+// The lists' entry point.  may_allocate: pinned memory for h_total may be
+// allocated by the call (once in a process).
+int segments_to_list(const void* d_segs, int64_t n, int64_t* d_offsets, void* d_voxels, int64_t capacity,
+                     int64_t* h_total, void* d_work, size_t work_bytes, void* stream, int kind, bool may_allocate);
 
 size_t list_workspace_bytes(int64_t n, int64_t capacity);
 ListWork list_workspace(void* d_work, int64_t n, int64_t capacity);

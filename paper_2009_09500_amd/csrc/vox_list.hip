@@ -175,13 +175,19 @@ __device__ __forceinline__ int32_t block_or(int32_t v, int64_t* lds) {
 }
 
 // The status word (range flags, capacity) and the one after it.
-__device__ __forceinline__ int32_t list_status(int32_t flags, int64_t total, int64_t capacity, int32_t* status) {
+// host: the status and the total for the caller as well (one lane).
+__device__ __forceinline__ int32_t list_status(int32_t flags, int64_t total, int64_t capacity, int32_t* status,
+                                               int64_t* host) {
     int32_t st = flags & kStatusOutOfRange;
     // (capacity > 0 exactly when voxels are wanted.)
     if (capacity > 0 && total > capacity) st |= kStatusCapacity;
     if (status) {
         status[0] = st;
         status[1] = flags & kListLong;
+        if (host) {
+            __hip_atomic_store(&host[0], (int64_t)st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&host[1], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
     return st;
 }
@@ -243,7 +249,7 @@ __global__ __launch_bounds__(kScanBlock) void k_list_scan(int64_t* __restrict__ 
                                                           int64_t nb, int64_t* __restrict__ offsets,
                                                           int64_t n, int64_t* __restrict__ total,
                                                           int32_t* __restrict__ status,
-                                                          int64_t capacity) {
+                                                          int64_t capacity, int64_t* host) {
     __shared__ int64_t lds[kScanBlock / kWave];
     int64_t carry = 0;
     int32_t flags = 0;
@@ -260,7 +266,7 @@ __global__ __launch_bounds__(kScanBlock) void k_list_scan(int64_t* __restrict__ 
     if (threadIdx.x == 0) {
         offsets[n] = carry;
         *total = carry;
-        list_status(f, carry, capacity, status);
+        list_status(f, carry, capacity, status, host);
     }
 }
 
@@ -285,7 +291,7 @@ __global__ __launch_bounds__(kCountBlock) void k_list_offsets(
     int64_t n, const uint32_t* __restrict__ counts, const int64_t* __restrict__ block_prefix,
     const int32_t* __restrict__ block_flags, int64_t nb, int64_t capacity,
     int64_t* __restrict__ offsets, int32_t* __restrict__ tile_seg, int64_t tile_limit,
-    int64_t* __restrict__ total, int32_t* __restrict__ status) {
+    int64_t* __restrict__ total, int32_t* __restrict__ status, int64_t* host) {
     __shared__ int64_t lds[kCountBlock / kWave];
     const int64_t base = (int64_t)blockIdx.x * kSegsPerCountBlock;
     int64_t carry, tot;
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(kCountBlock) void k_list_offsets(
         tot = block_sum<kCountBlock>(all, lds);
         fl = block_or<kCountBlock>(fl, lds);
         const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
-        const int32_t st = list_status(fl, tot, capacity, writer ? status : nullptr);
+        const int32_t st = list_status(fl, tot, capacity, writer ? status : nullptr, host);
         if (writer) {
             offsets[n] = tot;
             *total = tot;
@@ -344,7 +350,7 @@ __device__ __forceinline__ int32_t one_block_offsets(const int32_t* __restrict__
                                                      const uint32_t* __restrict__ counts, int64_t capacity,
                                                      bool store, int64_t* __restrict__ offsets,
                                                      int64_t* __restrict__ total_p, int32_t* __restrict__ status,
-                                                     int64_t (&c)[kCountPerThread], int64_t (&off)[kCountPerThread],
+                                                     int64_t* host, int64_t (&c)[kCountPerThread], int64_t (&off)[kCountPerThread],
                                                      int32_t& flags, int64_t& total) {
     __shared__ int64_t lds[kCountBlock / kWave];
     int64_t sum = 0;
@@ -371,7 +377,7 @@ __device__ __forceinline__ int32_t one_block_offsets(const int32_t* __restrict__
     flags = block_or<kCountBlock>(flag, lds);
     const int64_t ex = block_exclusive_sum<kCountBlock>(sum, lds, total);
     const bool writer = store && threadIdx.x == 0;
-    const int32_t st = list_status(flags, total, capacity, writer ? status : nullptr);
+    const int32_t st = list_status(flags, total, capacity, writer ? status : nullptr, host);
 #pragma unroll
     for (int s = 0; s < kCountPerThread; ++s) {
         const int64_t i = (int64_t)threadIdx.x * kCountPerThread + s;
@@ -392,10 +398,10 @@ template <bool kAligned8, int kKind>
 __global__ __launch_bounds__(kCountBlock) void k_list_one_block(
     const int32_t* __restrict__ segs, int64_t n, const uint32_t* __restrict__ counts,
     int64_t* __restrict__ offsets, int64_t* __restrict__ total_p, int32_t* __restrict__ status,
-    int64_t capacity) {
+    int64_t* host, int64_t capacity) {
     int64_t c[kCountPerThread], off[kCountPerThread], total;
     int32_t flags;
-    one_block_offsets<kAligned8, kKind>(segs, n, counts, capacity, true, offsets, total_p, status, c, off, flags,
+    one_block_offsets<kAligned8, kKind>(segs, n, counts, capacity, true, offsets, total_p, status, host, c, off, flags,
                                         total);
 }
 
@@ -478,6 +484,7 @@ struct ListHeader {
     int64_t* offsets;
     int64_t* total;
     int32_t* status;
+    int64_t* host;
     int64_t capacity;
 };
 
@@ -521,7 +528,7 @@ void k_list_voxels(
         int64_t c[kCountPerThread], off[kCountPerThread];
         int32_t flags;
         const int32_t st = one_block_offsets<kAligned8, sizeof(T) == 2 ? kListI16 : kListI32>(
-            segs, n, nullptr, header.capacity, blockIdx.x == 0, header.offsets, header.total, header.status, c, off,
+            segs, n, nullptr, header.capacity, blockIdx.x == 0, header.offsets, header.total, header.status, header.host, c, off,
             flags, total);
         if (st != 0 || j0 >= total) return;
         j1 = j0 + kListTile < total ? j0 + kListTile : total;
@@ -1259,10 +1266,10 @@ static void list_one_block(const int32_t* segs, int64_t n, bool aligned8, const 
     if (kKind == kListEuclid && n > 0) launch_euclid_counts(segs, n, aligned8, w, stream);
     if (aligned8)
         k_list_one_block<true, kKind><<<1, kCountBlock, 0, stream>>>(segs, n, w.counts, offsets, w.total, w.status,
-                                                                      capacity);
+                                                                      w.host, capacity);
     else
         k_list_one_block<false, kKind><<<1, kCountBlock, 0, stream>>>(segs, n, w.counts, offsets, w.total,
-                                                                       w.status, capacity);
+                                                                       w.status, w.host, capacity);
 }
 
 // Whether the tiles of a list with room for this many search for their
@@ -1290,7 +1297,7 @@ hipError_t launch_list_scan(const ListWork& w, int64_t n, int64_t* offsets, int6
     if (n >= 1 && w.nb <= kFusedScanMaxBlocks) return hipSuccess;  // done by the offsets kernel
     KernelTimer timer("list_scan", stream);
     k_list_scan<<<1, kScanBlock, 0, stream>>>(w.block_sums, w.block_flags, w.nb, offsets, n, w.total,
-                                              w.status, capacity);
+                                              w.status, capacity, w.host);
     return hipGetLastError();
 }
 
@@ -1305,11 +1312,11 @@ hipError_t launch_list_offsets(int64_t n, int64_t* offsets, const ListWork& w, i
     if (w.nb <= kFusedScanMaxBlocks)
         k_list_offsets<true><<<dim3((unsigned)w.nb), kCountBlock, 0, stream>>>(
             n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped,
-            w.total, w.status);
+            w.total, w.status, w.host);
     else
         k_list_offsets<false><<<dim3((unsigned)w.nb), kCountBlock, 0, stream>>>(
             n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped,
-            w.total, w.status);
+            w.total, w.status, w.host);
     return hipGetLastError();
 }
 
@@ -1353,7 +1360,7 @@ bool list_one_launch(int64_t n, int64_t capacity) {
 hipError_t launch_list_all(const int32_t* segs, int64_t n, bool aligned8, int64_t* offsets, const ListWork& w,
                            void* voxels, int64_t capacity, hipStream_t stream, ListKind kind) {
     KernelTimer timer("list_all", stream);
-    const ListHeader header{offsets, w.total, w.status, capacity};
+    const ListHeader header{offsets, w.total, w.status, w.host, capacity};
     if (kind == kListI32)
         list_voxels<int32_t, kTileAll>(segs, n, aligned8, offsets, w, static_cast<int32_t*>(voxels), w.ntiles,
                                        header, stream);

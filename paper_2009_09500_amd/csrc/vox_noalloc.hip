@@ -62,5 +62,6 @@ extern "C" vox_status vox_segments_to_list_noalloc(const vox_segment* d_segs, in
     void* ptr = nullptr;
     const vox_status st = device_scratch(&ptr);
     if (st != VOX_OK) return st;
-    return vox_segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, ptr, kScratchBytes, stream);
+    return (vox_status)vox::segments_to_list(d_segs, n, d_offsets, d_voxels, capacity, h_total, ptr, kScratchBytes,
+                                             stream, vox::kListI16, false);
 }

@@ -93,3 +93,39 @@ def test_list_of_few_segments(n, room, wide):
         got = to_host(vox)
         assert np.array_equal(got[: 3 * total].reshape(-1, 3), expect)
         assert np.all(got[3 * total:] == 77)
+
+
+@pytest.mark.parametrize("threads", [1, 6])
+def test_totals_from_threads(threads):
+    """Totals asked for by several threads at once, each on a stream of its own,
+    among calls that are refused."""
+    import threading
+    torch = pytest.importorskip("torch")
+    wrong = []
+
+    def work_of(t):
+        rng = np.random.default_rng(t)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for i in range(40):
+                n = int(rng.choice([0, 1, 700, 1024, 1025, 5000]))
+                segs = axis_aligned_mix(rng, rng.integers(0, 50, n)).reshape(-1, 6)
+                if n and i % 5 == 4:
+                    segs[n // 2, 0] = 40000
+                expect = int(oracle.offsets(segs)[-1])
+                s = to_dev(segs) if n else torch.zeros((0, 6), dtype=torch.int32, device=dev())
+                offs = torch.empty(n + 1, dtype=torch.int64, device=dev())
+                work = binding.workspace(binding.vox_list_workspace_bytes(n, 0), dev())
+                try:
+                    got = binding.vox_segments_to_list(s, offs, None, 0, work, want_total=True)
+                    ok = got == expect and not (n and i % 5 == 4)
+                except binding.VoxError as e:
+                    ok = e.status == binding.VOX_ERR_OUT_OF_RANGE and n > 0 and i % 5 == 4
+                if not ok:
+                    wrong.append((t, i, n))
+
+    pool = [threading.Thread(target=work_of, args=(t,)) for t in range(threads)]
+    for p in pool:
+        p.start()
+    for p in pool:
+        p.join()
+    assert not wrong
