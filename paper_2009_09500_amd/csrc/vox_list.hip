@@ -196,18 +196,18 @@ __device__ __forceinline__ int32_t list_status(int32_t flags, int64_t total, int
 // samples that start a new voxel) and their block sums; out-of-range flags
 // (int16 lists: a coordinate outside int16; int32 lists: an axis spanning
 // 2^30 or more), and whether a segment is longer than kFix16MaxN.
-template <bool kAligned8, int kKind>
-__global__ __launch_bounds__(kCountBlock) void k_list_count(const int32_t* __restrict__ segs,
-                                                            int64_t n, uint32_t* __restrict__ counts,
-                                                            int64_t* __restrict__ block_sums,
-                                                            int32_t* __restrict__ block_flags, int walk) {
-    __shared__ int64_t red[kCountBlock / kWave];
-    const int64_t base = (int64_t)blockIdx.x * kSegsPerCountBlock;
+template <bool kAligned8, int kKind, int kBlock>
+__global__ __launch_bounds__(kBlock) void k_list_count(const int32_t* __restrict__ segs,
+                                                       int64_t n, uint32_t* __restrict__ counts,
+                                                       int64_t* __restrict__ block_sums,
+                                                       int32_t* __restrict__ block_flags, int walk) {
+    __shared__ int64_t red[kBlock / kWave];
+    const int64_t base = (int64_t)blockIdx.x * (kBlock * kCountPerThread);
     int64_t sum = 0;
     int32_t flag = 0;
 #pragma unroll
     for (int s = 0; s < kCountPerThread; ++s) {
-        int64_t i = base + (int64_t)s * kCountBlock + threadIdx.x;
+        int64_t i = base + (int64_t)s * kBlock + threadIdx.x;
         if (i < n) {
             Seg g = load_seg<kAligned8>(segs, i);
             const bool inr = kKind == kListI32 ? span_below_2p30(g) : in_int16(g);
@@ -229,8 +229,8 @@ __global__ __launch_bounds__(kCountBlock) void k_list_count(const int32_t* __res
             sum += c > 0xFFFFFFFFll ? 0xFFFFFFFFll : c;
         }
     }
-    sum = block_sum<kCountBlock>(sum, red);
-    const int32_t f = block_or<kCountBlock>(flag, red);
+    sum = block_sum<kBlock>(sum, red);
+    const int32_t f = block_or<kBlock>(flag, red);
     if (threadIdx.x == 0) {
         block_sums[blockIdx.x] = sum;
         block_flags[blockIdx.x] = f;
@@ -272,42 +272,57 @@ __global__ __launch_bounds__(kScanBlock) void k_list_scan(int64_t* __restrict__ 
 
 // --------------------------------------------------- offsets and tile map
 
+// Segments from which the count and offsets kernels take 4096 a block of 1024
+// threads rather than 1024 a block of 256.
+constexpr int64_t kLargeBlockSegs = 262144;
+constexpr int kLargeBlock = 1024;
+
 // Count blocks up to this many: the offsets kernel sums the count blocks'
-// partials itself (every block reads all of them, at most 3 KiB) and the
+// partials itself (every block reads all of them, 12 bytes each) and the
 // scan kernel is not launched.  Measured per call: 100 000 segments 0.0255
-// -> 0.0225 ms, 5 000 segments 0.016 -> 0.0135 ms; at 1 024 blocks (10^6
-// segments) no gain for the Chebyshev lists and 4-6 % slower for the
-// Euclidean ones, so larger calls keep the scan kernel.
+// -> 0.0225 ms, 5 000 segments 0.016 -> 0.0135 ms (blocks of 256 threads);
+// 1 M segments of 65 voxels 0.0787 -> 0.0779 (of 1024).
 constexpr int64_t kFusedScanMaxBlocks = 256;
 
-// Same segment blocks as the count kernel.  Each sub-tile of kCountBlock
-// consecutive segments is scanned by the block; every segment then records
+// Same segment blocks as the count kernel, kCountPerThread consecutive ones a
+// thread, scanned by the block; every segment then records
 // itself as the first segment of each output tile whose first voxel it
 // holds.  kFused: the block's prefix, the total and the status come from the
 // count blocks' raw sums and flags (what k_list_scan would write; block 0
 // writes offsets[n], the total and the status word), else from k_list_scan.
-template <bool kFused>
-__global__ __launch_bounds__(kCountBlock) void k_list_offsets(
+template <bool kFused, int kBlock>
+__global__ __launch_bounds__(kBlock) void k_list_offsets(
     int64_t n, const uint32_t* __restrict__ counts, const int64_t* __restrict__ block_prefix,
     const int32_t* __restrict__ block_flags, int64_t nb, int64_t capacity,
     int64_t* __restrict__ offsets, int32_t* __restrict__ tile_seg, int64_t tile_limit,
     int64_t* __restrict__ total, int32_t* __restrict__ status, int64_t* host) {
-    __shared__ int64_t lds[kCountBlock / kWave];
-    const int64_t base = (int64_t)blockIdx.x * kSegsPerCountBlock;
+    __shared__ int64_t lds[kBlock / kWave];
+    static_assert(kCountPerThread == 4, "one 16-byte load of counts a thread");
+    const int64_t i0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kCountPerThread;
+    // (The counts are 256-byte aligned.)
+    uint4 c4 = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 + 3 < n) {
+        c4 = *reinterpret_cast<const uint4*>(counts + i0);
+    } else if (i0 < n) {
+        c4.x = counts[i0];
+        if (i0 + 1 < n) c4.y = counts[i0 + 1];
+        if (i0 + 2 < n) c4.z = counts[i0 + 2];
+    }
+    const uint32_t c[kCountPerThread] = {c4.x, c4.y, c4.z, c4.w};
     int64_t carry, tot;
     bool tiles;  // only needed when voxels will be written
     if constexpr (kFused) {
         int64_t pre = 0, all = 0;
         int32_t fl = 0;
-        for (int64_t b = threadIdx.x; b < nb; b += kCountBlock) {
+        for (int64_t b = threadIdx.x; b < nb; b += kBlock) {
             const int64_t v = block_prefix[b];
             all += v;
             pre += b < (int64_t)blockIdx.x ? v : 0;
             fl |= block_flags[b];
         }
-        carry = block_sum<kCountBlock>(pre, lds);
-        tot = block_sum<kCountBlock>(all, lds);
-        fl = block_or<kCountBlock>(fl, lds);
+        carry = block_sum<kBlock>(pre, lds);
+        tot = block_sum<kBlock>(all, lds);
+        fl = block_or<kBlock>(fl, lds);
         const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
         const int32_t st = list_status(fl, tot, capacity, writer ? status : nullptr, host);
         if (writer) {
@@ -321,22 +336,20 @@ __global__ __launch_bounds__(kCountBlock) void k_list_offsets(
         tot = *total;
     }
     const int64_t ntiles = tot < tile_limit * kListTile ? (tot + kListTile - 1) / kListTile : tile_limit;
+    int64_t sub;
+    int64_t off = carry + block_exclusive_sum<kBlock>((int64_t)c[0] + c[1] + c[2] + c[3], lds, sub);
+#pragma unroll
     for (int s = 0; s < kCountPerThread; ++s) {
-        int64_t i = base + (int64_t)s * kCountBlock + threadIdx.x;
-        int64_t c = i < n ? (int64_t)counts[i] : 0;
-        int64_t sub;
-        int64_t ex = block_exclusive_sum<kCountBlock>(c, lds, sub);
-        int64_t off = carry + ex;
-        if (i < n) {
-            offsets[i] = off;
+        if (i0 + s < n) {
+            offsets[i0 + s] = off;
             if (tiles) {
                 int64_t t0 = (off + kListTile - 1) / kListTile;
-                int64_t t1 = (off + c - 1) / kListTile;  // inclusive
+                int64_t t1 = (off + c[s] - 1) / kListTile;  // inclusive
                 if (t1 >= ntiles) t1 = ntiles - 1;
-                for (int64_t t = t0; t <= t1; ++t) tile_seg[t] = (int32_t)i;
+                for (int64_t t = t0; t <= t1; ++t) tile_seg[t] = (int32_t)(i0 + s);
             }
         }
-        carry += sub;
+        off += c[s];
     }
 }
 
@@ -404,6 +417,8 @@ __global__ __launch_bounds__(kCountBlock) void k_list_one_block(
     one_block_offsets<kAligned8, kKind>(segs, n, counts, capacity, true, offsets, total_p, status, host, c, off, flags,
                                         total);
 }
+
+static_assert(kLargeBlockSegs <= kFusedScanMaxBlocks * kSegsPerCountBlock, "small blocks are always fused");
 
 // ------------------------------------------------------------ voxel tiles
 
@@ -1191,7 +1206,7 @@ ListWork list_workspace(void* d_work, int64_t n, int64_t capacity) {
     w.counts = reinterpret_cast<uint32_t*>(p);
     p += align_up((size_t)(n > 0 ? n : 1) * sizeof(uint32_t));
     w.tile_seg = reinterpret_cast<int32_t*>(p);
-    w.nb = nb;
+    w.nb = n > kLargeBlockSegs ? (n + kLargeBlock * kCountPerThread - 1) / (kLargeBlock * kCountPerThread) : nb;
     w.ntiles = (capacity + kListTile - 1) / kListTile;
     return w;
 }
@@ -1239,12 +1254,19 @@ static void list_count(const int32_t* segs, int64_t n, bool aligned8, const List
     if (kKind == kListEuclid && n > 0 && !walk) launch_euclid_counts(segs, n, aligned8, w, stream);
     // n == 0: one block that writes a zero sum and no flag.
     dim3 grid(n == 0 ? 1u : (unsigned)w.nb);
-    if (aligned8)
-        k_list_count<true, kKind><<<grid, kCountBlock, 0, stream>>>(segs, n, w.counts, w.block_sums,
-                                                                     w.block_flags, walk);
+    auto launch = [&](auto block) {
+        constexpr int kBlock = decltype(block)::value;
+        if (aligned8)
+            k_list_count<true, kKind, kBlock><<<grid, kBlock, 0, stream>>>(segs, n, w.counts, w.block_sums,
+                                                                           w.block_flags, walk);
+        else
+            k_list_count<false, kKind, kBlock><<<grid, kBlock, 0, stream>>>(segs, n, w.counts, w.block_sums,
+                                                                            w.block_flags, walk);
+    };
+    if (n > kLargeBlockSegs)
+        launch(std::integral_constant<int, kLargeBlock>{});
     else
-        k_list_count<false, kKind><<<grid, kCountBlock, 0, stream>>>(segs, n, w.counts, w.block_sums,
-                                                                      w.block_flags, walk);
+        launch(std::integral_constant<int, kCountBlock>{});
 }
 
 hipError_t launch_list_count(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w,
@@ -1309,14 +1331,18 @@ hipError_t launch_list_offsets(int64_t n, int64_t* offsets, const ListWork& w, i
     // entries a thread each would write: the tiles search.)
     const int64_t mapped = list_searches(n, tiles) ? 0 : tiles;
     KernelTimer timer("list_offsets", stream);
-    if (w.nb <= kFusedScanMaxBlocks)
-        k_list_offsets<true><<<dim3((unsigned)w.nb), kCountBlock, 0, stream>>>(
-            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped,
-            w.total, w.status, w.host);
+    auto launch = [&](auto fused, auto block) {
+        constexpr int kBlock = decltype(block)::value;
+        k_list_offsets<decltype(fused)::value, kBlock><<<dim3((unsigned)w.nb), kBlock, 0, stream>>>(
+            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped, w.total, w.status,
+            w.host);
+    };
+    if (n <= kLargeBlockSegs)
+        launch(std::true_type{}, std::integral_constant<int, kCountBlock>{});
+    else if (w.nb <= kFusedScanMaxBlocks)
+        launch(std::true_type{}, std::integral_constant<int, kLargeBlock>{});
     else
-        k_list_offsets<false><<<dim3((unsigned)w.nb), kCountBlock, 0, stream>>>(
-            n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped,
-            w.total, w.status, w.host);
+        launch(std::false_type{}, std::integral_constant<int, kLargeBlock>{});
     return hipGetLastError();
 }
 
