@@ -168,8 +168,8 @@ constexpr int kWStatus = 0;    // status bits (kStatus*)
 constexpr int kWOk = 2;        // 1 when the brick kernels may run
 constexpr int kWDirectAll = 3; // 1: the direct kernels serve every scene (records do not fit)
 constexpr int kWQueues = 4;    // 8 work queues of the fill
-constexpr int kWItems = 12;    // the fill's work items (k_brick_base)
-constexpr int kWSplit = 13;    // bricks cut into several work items (k_brick_base)
+constexpr int kWItems = 12;    // the fill's work items
+constexpr int kWSplit = 13;    // bricks cut into several work items
 constexpr int kWPieces = 16;   // uint64: piece records the call needed (information)
 constexpr size_t kWorkTable = kAlign;
 

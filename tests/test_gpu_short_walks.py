@@ -71,3 +71,23 @@ def test_batch_with_many_bricks(dims, euclid):
     assert status == binding.VOX_OK
     b.check()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("scenes", [1, 2, 64, 65, 256, 257, 1025, 4100])
+def test_batch_of_many_scenes(scenes):
+    """Every row finds its scene: empty scenes, scenes of several rows, and
+    scenes that the direct kernel serves (rows of odd width) among them."""
+    import torch
+    from tests.test_gpu_batch import Batch, run_batch
+    rng = np.random.default_rng(scenes)
+    specs = []
+    for i in range(scenes):
+        dims = [(64, 20, 9), (33, 7, 5), (32, 4, 70), (96, 70, 3)][i % 4]
+        n = 9000 if i in (1, scenes // 2, scenes - 1) else int(rng.choice([0, 1, 7, 20]))
+        p = [np.stack([rng.integers(0, d, n) for d in dims], 1) for _ in range(2)]
+        specs.append((np.concatenate(p, 1).astype(np.int32), dims, binding.VOX_GRID_CLEAR, None, i % 3 == 0))
+    b = Batch(specs)
+    status, _ = run_batch(b)
+    assert status == binding.VOX_OK
+    b.check()
+    torch.cuda.empty_cache()
