@@ -26,15 +26,15 @@ __global__ __launch_bounds__(kGridBlock) void k_grid_clear(uint32_t* __restrict_
 }
 
 // All segments of one volume (direct_segments, vox_direct.h).
-template <bool kAligned8, bool kEuclid>
+template <bool kAligned8, bool kEuclid, bool kRuns>
 __global__ __launch_bounds__(kGridBlock) void k_grid_direct(const int32_t* __restrict__ segs, int64_t n,
                                                             int32_t dx, int32_t dy, int32_t dz,
                                                             uint32_t* __restrict__ grid,
                                                             int32_t* __restrict__ counts,
                                                             int32_t* __restrict__ status) {
-    direct_segments<kAligned8, kEuclid>(segs, n, dx, dy, dz, grid, counts, status,
-                                        (int64_t)blockIdx.x * (kGridBlock / kWave) + threadIdx.x / kWave,
-                                        (int64_t)gridDim.x * (kGridBlock / kWave));
+    direct_segments<kAligned8, kEuclid, kRuns>(segs, n, dx, dy, dz, grid, counts, status,
+                                               (int64_t)blockIdx.x * (kGridBlock / kWave) + threadIdx.x / kWave,
+                                               (int64_t)gridDim.x * (kGridBlock / kWave));
 }
 
 // ------------------------------------------------------------------- slabs
@@ -387,20 +387,25 @@ hipError_t launch_grid(const int32_t* segs, int64_t n, bool aligned8, int32_t dx
     if (blocks > 16384) blocks = 16384;
     dim3 gridDim((unsigned)blocks);
     KernelTimer timer(euclid ? "grid_direct_euclid" : "grid_direct", stream);
+    auto direct = [&](auto a8, auto eu) {
+        constexpr bool kA8 = decltype(a8)::value, kEu = decltype(eu)::value;
+        if (n > kRunsMinSegments)
+            k_grid_direct<kA8, kEu, true><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
+                                                                              w.status);
+        else
+            k_grid_direct<kA8, kEu, false><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
+                                                                               w.status);
+    };
     if (euclid) {
         if (aligned8)
-            k_grid_direct<true, true><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
-                                                                          w.status);
+            direct(std::true_type{}, std::true_type{});
         else
-            k_grid_direct<false, true><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
-                                                                           w.status);
+            direct(std::false_type{}, std::true_type{});
     } else {
         if (aligned8)
-            k_grid_direct<true, false><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
-                                                                           w.status);
+            direct(std::true_type{}, std::false_type{});
         else
-            k_grid_direct<false, false><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
-                                                                            w.status);
+            direct(std::false_type{}, std::false_type{});
     }
     return hipGetLastError();
 }
