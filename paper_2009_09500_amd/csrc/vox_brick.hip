@@ -2097,8 +2097,10 @@ void k_brick_fill(uint8_t* __restrict__ work) {
                             r0 |= dst[0];
                             r1 |= dst[row_words / 4];
                         }
-                        dst[0] = r0;
-                        dst[row_words / 4] = r1;
+                        // (Whole 64-byte blocks: past the caches, which the
+                        // records need.  2048^3: 0.837 against 0.905 ms.)
+                        __builtin_nontemporal_store(r0, dst);
+                        __builtin_nontemporal_store(r1, dst + row_words / 4);
                     }
                     dst += dst_step;
                 }
