@@ -67,8 +67,7 @@ typedef enum vox_status {
  * the voxels are ORed into the volume's current contents. */
 #define VOX_GRID_CLEAR 1u
 /* Grid flag: the paper's literal length of eq. (1), N = int(|E - S|) (see
- * vox_segments_to_list_euclid), instead of max |d_a|.  Such calls take the
- * direct path (one device atomic per voxel, no LDS bricks). */
+ * vox_segments_to_list_euclid), instead of max |d_a|. */
 #define VOX_GRID_EUCLID 2u
 
 /* ---------------------------------------------------------------- lists */
@@ -91,6 +90,8 @@ size_t vox_list_workspace_bytes(int64_t n, int64_t capacity);
  *              stream once, stores the total, and returns
  *              VOX_ERR_OUT_OF_RANGE / VOX_ERR_CAPACITY from the device
  *              status instead of VOX_OK.
+ *              (The first such call of a process also allocates a page of
+ *              pinned host memory, which the totals come through.)
  *   d_work     workspace, >= vox_list_workspace_bytes(n, capacity) bytes,
  *              256-byte aligned.
  *
@@ -109,7 +110,7 @@ vox_status vox_segments_to_list(const vox_segment *d_segs, int64_t n,
  * voxel of the sample before it dropped (with this N two samples can share
  * a voxel).  d_offsets[i] counts the voxels kept; arguments, workspace size
  * (vox_list_workspace_bytes), ownership and errors as for
- * vox_segments_to_list.  Sixteen lanes share a segment's samples. */
+ * vox_segments_to_list. */
 vox_status vox_segments_to_list_euclid(const vox_segment *d_segs, int64_t n,
                                        int64_t *d_offsets, int16_t *d_voxels,
                                        int64_t capacity, int64_t *h_total,
@@ -181,8 +182,9 @@ size_t vox_grid_workspace_bytes(int64_t n, int32_t dim_x, int32_t dim_y, int32_t
  * multiple of 32 and every side at most 16384 (and a brick count within the
  * library's limit; with VOX_GRID_EUCLID also a volume diagonal
  * sqrt((dim_x-1)^2 + (dim_y-1)^2 + (dim_z-1)^2) below 16385) fill LDS
- * bricks; the others take the direct path (one device atomic per voxel).
- * The output is the same. */
+ * bricks.  Of the others, small ones give every workgroup a run of the volume
+ * in LDS (one launch), and the rest take the direct path (device atomics on
+ * the volume's words).  The output is the same. */
 vox_status vox_segments_to_grid(const vox_segment *d_segs, int64_t n,
                                 int32_t dim_x, int32_t dim_y, int32_t dim_z,
                                 uint32_t *d_grid, int32_t *d_counts, uint32_t flags,
@@ -283,7 +285,7 @@ size_t vox_workspace_bytes(int op, int64_t n_segments, int32_t n_scenes);
  * most 16384 and at most 16384 bricks (with VOX_GRID_EUCLID, a volume
  * diagonal below 16385) take the LDS brick kernels; the others (and every
  * scene, when the piece records of the call do not fit the workspace) take
- * direct kernels with one device atomic per voxel.  The output never depends
+ * a direct kernel with one device atomic per voxel.  The output never depends
  * on which.
  *
  * Reads no device memory on the host, synchronises nothing and allocates

@@ -1865,8 +1865,8 @@ struct RoundQueue {
 // chunks in four length classes within the group, digests passed between lanes
 // by ds_bpermute), and rows are written in pairs (see the flush): 4 M segments
 // of up to 2048 voxels into 2048^3 (19.0 M records, 721.7 M voxels, 1 GiB)
-// 0.61 -> 0.50 ms, VALU wave instructions 227 -> 160 M; 100 000 into 512^3
-// 19.8 -> 17.5 us.
+// 0.61 -> 0.47 ms, VALU wave instructions 227 -> 169 M; 100 000 into 512^3
+// 20.1 -> 13.4 us.
 template <int LGX, int LGY, int LGZ, int kWgs>
 __global__ __launch_bounds__((FillCfg<LGX, LGY, LGZ, kWgs>::kBlock), 4)  // 16 waves a CU
 void k_brick_fill(uint8_t* __restrict__ work) {
@@ -1894,9 +1894,11 @@ void k_brick_fill(uint8_t* __restrict__ work) {
     q.extra = q.items - NB;
     q.cut = *wv.n_split != 0u;
     // Units of two while every workgroup still gets at least four of them:
-    // they halve the partial writes (2048^3: 0.95 against 1.06 ms a call), but
-    // with four bricks a workgroup (eight wireframes in 512^3) the coarser
-    // shares cost more (159 against 141 us).
+    // they halve the partial writes (2048^3: 0.84 against 1.06 ms a call).  With
+    // fewer the coarser shares cost more, except where all bricks are alike (at
+    // least two of them: 12 wireframes in 512^3 151 against 147 us, 400 000
+    // segments in 1024^3 434 against 419, 143 small scenes 450 against 426, but
+    // eight wireframes 112.5 against 118).
     const bool two = q.items >= kPairItems * gridDim.x;
     q.units = two ? (q.items + 1u) >> 1 : q.items;
     q.lg = two ? 2u : 3u;

@@ -309,8 +309,10 @@ __host__ __device__ inline bool brick_geometry(int32_t dx, int32_t dy, int32_t d
 // total / T <= kSplitShares, and so do the cut bricks.
 // kSplitMinRecords: the flush of a part (a word at a time, atomics) costs
 // about as much as the bits of some thousand short pieces: eight wireframes in
-// 512^3 (0.5 M edges of a few voxels) take 152 us a batch with 4096, 141 us
-// with 8192 or 16384.
+// 512^3 (0.5 M edges of a few voxels) take 129 us a batch with 4096, 118 with
+// 8192.  kSplitShares: 2048 balances 256 scenes of 64^3 to 512^3 better (1333
+// against 1400 us) but cuts more than it pays in others (143 scenes of 64^3 and
+// 128^3: 441 against 426).
 constexpr uint32_t kSplitShares = 1024;
 constexpr uint32_t kSplitMinRecords = 8192;
 constexpr uint32_t kMaxExtraItems = kSplitShares;

@@ -287,10 +287,12 @@ static hipError_t launch_slabs(const int32_t* segs, int64_t n, int32_t dx, int32
     return hipGetLastError();
 }
 
-// Plain calls with at most this many segments do not take the brick path:
-// one or two launches beat the brick pipeline's five there (measured on one
-// MI355X: 1 000 segments in 256^3, 11 vs 38 us a call; one segment, 10 vs
-// 30 us; 16 384 segments in 512^3, 44 vs 77 us).
+// Plain calls with at most this many segments do not take the brick path, whose
+// three to five launches and three passes cost 30 us with any segments at all
+// (1 000 segments in 256^3: 7 against 30 us a call).  With more it depends on
+// their lengths, which the host does not know: 16 384 of log-uniform length in
+// 512^3 / 960^3 take 20 / 77 us here and 38 / 122 on the brick path, but uniform
+// ones 48 / 312 and 42 / 133.
 constexpr int64_t kDirectMaxSegments = 16384;
 
 // The brick path serves calls with more segments than that, on volumes whose
