@@ -154,9 +154,9 @@ VALU_PEAK = CUS * CLOCK_HZ        # wave64 VALU instructions per second (one per
 # an FMA as two and packed fp32 as two more).
 ALU_PEAK_TOPS = CUS * 64 * CLOCK_HZ / 1e12
 # The fill's algorithmic ALU work per voxel: the stepping of eq. (3) with the
-# minor error terms in packed halves (packed add, packed shift, packed
-# multiply-add, dot product, dominant stride) and the LDS word and bit of the
-# voxel (shift, mask, shift): 8 lane operations; the LDS OR is not ALU work.
+# minor axes as 32-bit fractions (two adds with carry, two selects of a stride,
+# one three-way add) and the LDS word and bit of the voxel (shift, mask,
+# shift): 8 lane operations; the LDS OR is not ALU work.
 FILL_OPS_PER_VOXEL = 8
 
 
