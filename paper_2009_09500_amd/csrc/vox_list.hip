@@ -196,8 +196,9 @@ __device__ __forceinline__ int32_t list_status(int32_t flags, int64_t total, int
 // samples that start a new voxel) and their block sums; out-of-range flags
 // (int16 lists: a coordinate outside int16; int32 lists: an axis spanning
 // 2^30 or more), and whether a segment is longer than kFix16MaxN.
+// (64 VGPRs at most, so that two blocks of 1024 run on a CU.)
 template <bool kAligned8, int kKind, int kBlock>
-__global__ __launch_bounds__(kBlock) void k_list_count(const int32_t* __restrict__ segs,
+__global__ __launch_bounds__(kBlock, kBlock == 1024 ? 8 : 1) void k_list_count(const int32_t* __restrict__ segs,
                                                        int64_t n, uint32_t* __restrict__ counts,
                                                        int64_t* __restrict__ block_sums,
                                                        int32_t* __restrict__ block_flags, int walk) {
@@ -915,8 +916,9 @@ __device__ __forceinline__ uint32_t euclid_voxels_any(const Seg& g, int16_t* out
 // Lists with the Euclidean N of eq. (1).  A wave takes up to 64 consecutive
 // segments: a lane each for what depends on the segment alone (LDS), then kL
 // lanes each for the samples, a run of up to kEuclidRun consecutive ones a
-// lane; kL is the least that gives all but four of the wave's segments one run
-// a lane, and a longer segment takes all lanes, window by window.  Per axis the
+// lane; a longer segment takes all lanes, window by window, and kL is what gives
+// the wave the fewest passes (2 M segments of 1 to 45 samples: 0.109 ms, 0.152
+// where all but four of the wave's segments had to fit one run a lane).  Per axis the
 // coordinate at sample k is the high word of start + k slope (64 bits), the
 // fraction its low word, and a step's carry out of the fraction is a move of
 // the axis, so the kept samples of a run are counted with three adds a sample,
@@ -1097,12 +1099,18 @@ struct EuclidLists {
     __device__ __forceinline__ void groups(const int32_t* __restrict__ segs, int64_t i0, uint32_t cnt, uint32_t N) {
         constexpr uint32_t kSlots = kWave / kL;
         const uint64_t longer = __builtin_amdgcn_ballot_w64((uint32_t)__lane_id() < cnt && N >= kL * kEuclidRun);
-        for (uint32_t s = 0; s < cnt; s += kSlots) {
-            if (kL < kWave && ((longer >> s) & (~0ull >> (kWave - kSlots))) == 0) {
-                to += run<kL>(s, cnt, 0u, place(to));
-                flush(false);
+        for (uint32_t s = 0; s < cnt;) {
+            const uint64_t rest = longer >> s;
+            if ((rest & 1u) != 0) {
+                one(segs, i0, s, __builtin_amdgcn_readlane(N, s));
+                ++s;
             } else {
-                for (uint32_t t = s; t < cnt && t < s + kSlots; ++t) one(segs, i0, t, __builtin_amdgcn_readlane(N, t));
+                // Those up to the next longer one, as many as the lanes take.
+                uint32_t end = rest ? s + (uint32_t)__builtin_ctzll(rest) : cnt;
+                end = end < s + kSlots ? end : s + kSlots;
+                to += run<kL>(s, end, 0u, place(to));
+                flush(false);
+                s = end;
             }
         }
     }
@@ -1132,12 +1140,20 @@ struct EuclidLists {
         e.start = 0x80000000u - (uint32_t)(0x1p31 * rcp_n);
         w.seg[lane] = e;
         fence();
-        // Lanes a segment: all but a few of the wave's segments in one pass.
-        uint32_t lanes = 1;
-        while (lanes < (uint32_t)kWave &&
-               (lanes * cnt <= kWave / 2u ||
-                __popcll(__builtin_amdgcn_ballot_w64(lane < cnt && N >= lanes * kEuclidRun)) > 4))
-            lanes *= 2u;
+        // Lanes a segment: the fewest passes over the wave's segments, those
+        // that are longer than one run a lane one by one (and half a pass
+        // lost before each), the others 64 / lanes at a time.
+        uint32_t lanes = kWave, best = ~0u;
+#pragma unroll
+        for (uint32_t l = 1; l <= (uint32_t)kWave; l *= 2u) {
+            const uint32_t big = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(lane < cnt && N >= l * kEuclidRun));
+            const uint32_t cost = big * 64u + (cnt - big) * l + (big < cnt - big ? big : cnt - big) * 32u;
+            // (As many lanes as spread few segments over the wave.)
+            if (l * cnt > kWave / 2u && cost < best) {
+                best = cost;
+                lanes = l;
+            }
+        }
         switch (lanes) {
             case 1: groups<1>(segs, i0, cnt, N); break;
             case 2: groups<2>(segs, i0, cnt, N); break;
@@ -1246,11 +1262,17 @@ static void launch_euclid_counts(const int32_t* segs, int64_t n, bool aligned8, 
         euclid_counts<64>(segs, n, aligned8, w.counts, stream);
 }
 
+constexpr int64_t kWalkInCountSegs = 1048576;
+
 template <int kKind>
 static void list_count(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w, hipStream_t stream) {
-    // With one lane a segment the count kernel walks the segments itself, one
-    // launch fewer (1 M segments of 64 samples: 0.031 against 0.046 ms).
-    const int walk = kKind == kListEuclid && n > 0 && euclid_count_lanes(n, w) == 1 ? 1 : 0;
+    // With one lane a segment the count kernel may walk the segments itself, one
+    // launch fewer, but four a thread: where that still fills the chip (1 M
+    // segments of 64 samples 0.146 against 0.150 ms a call), or for short ones.
+    // 100 000 segments of 1 to 960 samples, whose waves walk as long as their
+    // longest: 0.209 against 0.105 ms a call.
+    const bool one_lane = kKind == kListEuclid && n > 0 && euclid_count_lanes(n, w) == 1;
+    const int walk = one_lane && (n >= kWalkInCountSegs || w.ntiles * kListTile <= 32 * n) ? 1 : 0;
     if (kKind == kListEuclid && n > 0 && !walk) launch_euclid_counts(segs, n, aligned8, w, stream);
     // n == 0: one block that writes a zero sum and no flag.
     dim3 grid(n == 0 ? 1u : (unsigned)w.nb);
@@ -1417,7 +1439,10 @@ static void list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, co
 // the general form with a wave each: its stores are whole rounds of 64 samples
 // and it needs no LDS, hence twice the waves.  68 M voxels in segments of 500 /
 // 1000 / 2000 samples: 0.130 / 0.118 / 0.107 ms against 0.127 / 0.126 / 0.127.
+// So do few segments, of which a wave would have one anyway (3 394 of 1 to 2048
+// samples 24.1 against 28.3 us a call, 7 000 of 30 16.4 / 18.8).
 constexpr int64_t kEuclidAnyVoxels = 750;
+constexpr int64_t kEuclidAnySegs = 8192;
 
 static void list_voxels_euclid_any(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
                                    const ListWork& w, int16_t* voxels, hipStream_t stream) {
@@ -1435,7 +1460,7 @@ hipError_t launch_list_voxels_euclid(const int32_t* segs, int64_t n, bool aligne
                                      const ListWork& w, int16_t* voxels, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     KernelTimer timer("list_voxels_euclid", stream);
-    if (w.ntiles * kListTile / n > kEuclidAnyVoxels)
+    if (n < kEuclidAnySegs || w.ntiles * kListTile / n > kEuclidAnyVoxels)
         list_voxels_euclid_any(segs, n, aligned8, offsets, w, voxels, stream);
     else
         list_voxels_euclid(segs, n, aligned8, offsets, w, voxels, stream);
