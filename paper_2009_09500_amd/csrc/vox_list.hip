@@ -1422,7 +1422,11 @@ hipError_t launch_list_all(const int32_t* segs, int64_t n, bool aligned8, int64_
 // the chip.
 static void list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
                                const ListWork& w, int16_t* voxels, hipStream_t stream) {
-    int64_t per = n / 8192;
+    // (Waves in all, by the voxels a segment: short ones gain more from sharing.
+    // 2048 / 4096 / 8192: 30 000 segments of 20 samples 18.2 / 19.2 / 22.6 us a
+    // call, 20 000 of 50 21.3 / 20.2 / 23.2, 48 000 of 1 to 2048 115 / 88 / 84.)
+    const int64_t avg = w.ntiles * kListTile / n;
+    int64_t per = n / (avg <= 32 ? 2048 : (avg <= 64 ? 4096 : 8192));
     per = per < 1 ? 1 : (per > kWave ? kWave : per);
     const int64_t segs_per_block = per * (kCountBlock / kWave);
     int64_t blocks = (n + segs_per_block - 1) / segs_per_block;
@@ -1439,10 +1443,11 @@ static void list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, co
 // the general form with a wave each: its stores are whole rounds of 64 samples
 // and it needs no LDS, hence twice the waves.  68 M voxels in segments of 500 /
 // 1000 / 2000 samples: 0.130 / 0.118 / 0.107 ms against 0.127 / 0.126 / 0.127.
-// So do few segments, of which a wave would have one anyway (3 394 of 1 to 2048
-// samples 24.1 against 28.3 us a call, 7 000 of 30 16.4 / 18.8).
+// So do few segments, which do not fill the chip otherwise (3 394 of 1 to 2048
+// samples 24.1 against 28.3 us a call, 10 885 of 53 18.8 / 23.2; at 20 000 of 50
+// 21.6 / 20.2).
 constexpr int64_t kEuclidAnyVoxels = 750;
-constexpr int64_t kEuclidAnySegs = 8192;
+constexpr int64_t kEuclidAnySegs = 16384;
 
 static void list_voxels_euclid_any(const int32_t* segs, int64_t n, bool aligned8, const int64_t* offsets,
                                    const ListWork& w, int16_t* voxels, hipStream_t stream) {

@@ -51,7 +51,7 @@ def test_euclid_fixed_point_bound(longest):
 @pytest.mark.parametrize("lanes", [1, 2, 4, 8, 16, 32, 64])
 def test_euclid_lanes(lanes):
     rng = np.random.default_rng(lanes)
-    n = max(65536 // lanes, 8192) + 1
+    n = max(65536 // lanes, 16384) + 1
     lengths = rng.integers(0, RUN * lanes + 2, n)
     lengths[: n // 2] = np.minimum(lengths[: n // 2], RUN * lanes * 4 // 7)
     lengths[1] = RUN * lanes - 1
@@ -62,12 +62,12 @@ def test_euclid_lanes(lanes):
     assert_list(axis_aligned_mix(rng, lengths))
 
 
-@pytest.mark.parametrize("n", [8191, 8192, 8193, 70_000])
+@pytest.mark.parametrize("n", [16383, 16384, 16385, 70_000])
 def test_euclid_mixed_lengths(n):
     """Waves of segments of every length in turn, a point to a thousand voxels,
     on both sides of the form with a wave a segment."""
     rng = np.random.default_rng(n)
-    assert_list(axis_aligned_mix(rng, np.exp(rng.random(n) * np.log(1000.0 if n < 10_000 else 60.0)).astype(int) - 1))
+    assert_list(axis_aligned_mix(rng, np.exp(rng.random(n) * np.log(1000.0 if n < 20_000 else 60.0)).astype(int) - 1))
 
 
 @pytest.mark.parametrize("n", [1, 3, 600])
