@@ -256,13 +256,14 @@ static int64_t slab_words(int64_t nwords) {
 // 1 us a thousand (16 384 segments of log-uniform length: 17 us in 256 runs,
 // 20 us in 512; direct 22 and 44 us), so their product is bounded; more than
 // 512 runs (64 KiB each) lose against the direct form (1000 x 700 x 600, 4 000
-// short segments 33 against 28 us), and so do many segments in a small volume,
-// whose direct atomics are few and stay in the L2 (64^3, 16 384 short ones 15
-// against 11 us; 4 000 of them 8.5 against 11).
+// short segments 33 against 28 us), and so do more than some segments in a small
+// volume, whose direct atomics are few and stay in the L2 (96^3, uniform ones:
+// 1 000 6.9 against 8.6 us, 2 000 10.3 / 8.4, 4 000 16.0 / 12.4; of log-uniform
+// length 6.5 / 8.3, 7.2 / 8.3, 8.3 / 8.5).
 constexpr int64_t kSlabMaxTests = int64_t(1) << 23;
 constexpr int64_t kSlabMaxRuns = 512;
 constexpr int64_t kSlabSmallVolume = 65536;  // words
-constexpr int64_t kSlabSmallSegments = 8192;
+constexpr int64_t kSlabSmallSegments = 1536;
 
 static bool use_slabs(int64_t n, int32_t dx, int32_t dy, int32_t dz, bool euclid, bool counts) {
     // (The Euclidean counts need whole walks; bits relative to a run, within

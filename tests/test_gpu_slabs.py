@@ -96,7 +96,7 @@ def test_out_of_volume_segments():
     check(segs, dims, clear=False, out=2)
 
 
-@pytest.mark.parametrize("dims,n", [((64, 64, 64), 8192), ((64, 64, 64), 8193), ((99, 250, 160), 16384),
+@pytest.mark.parametrize("dims,n", [((64, 64, 64), 1536), ((64, 64, 64), 1537), ((64, 64, 64), 8193), ((99, 250, 160), 16384),
                                     ((300, 299, 187), 32768), ((300, 299, 187), 32769),
                                     ((801, 800, 426), 12000)])
 def test_sides_of_the_rule(dims, n):
