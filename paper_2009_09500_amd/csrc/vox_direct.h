@@ -13,15 +13,19 @@ namespace vox {
 
 // ORs the bits of neighbouring lanes of 16 with the same word together; true in
 // the last lane of each such run, which then holds them.  `in`: the lane has a
-// sample (the segment's first lanes do), `end`: its last one.  (Words: the low
-// halves of addresses that differ by far less than 2^32 among the samples; a
-// sample may hold no bit of its own.)  Atomics bound the direct form, about 25 G a
+// sample (the segment's first lanes do), `end`: its last one.  (A sample may hold
+// no bit of its own.)  Atomics bound the direct form, about 25 G a
 // second, and a segment along x sets up to 16 neighbouring bits: 50 000 uniform
 // segments in 300x251x199 0.203 ms against 0.251, 16 384 in 960^3 0.312 / 0.345.
 // Few segments are bound by the latency of their waves instead (log-uniform
 // lengths in 960^3: 1000 0.0162 / 0.0122, 8000 0.0371 / 0.0364, 16 000 0.0619 /
-// 0.0633), so fewer than kRunsMinSegments set bit by bit.
+// 0.0633), so fewer than kRunsMinSegments set bit by bit.  So do volumes of
+// more than kRunsMaxWords words, whose samples can lie a multiple of 2^32 words
+// apart (in 2^19 x 2^18 x 2 one z step does), for words are told apart by the low
+// halves of their indexes.
 constexpr int64_t kRunsMinSegments = 8192;
+constexpr int64_t kRunsMaxWords = int64_t(1) << 32;
+inline bool direct_runs(int64_t n, int64_t nwords) { return n > kRunsMinSegments && nwords <= kRunsMaxWords; }
 __device__ __forceinline__ bool or_runs(uint32_t word, bool in, bool end, uint32_t& bits) {
     static_assert(kSampleLanes == 16, "one DPP row a segment");
     auto step = [&](auto shift) {

@@ -392,7 +392,7 @@ hipError_t launch_grid(const int32_t* segs, int64_t n, bool aligned8, int32_t dx
     KernelTimer timer(euclid ? "grid_direct_euclid" : "grid_direct", stream);
     auto direct = [&](auto a8, auto eu) {
         constexpr bool kA8 = decltype(a8)::value, kEu = decltype(eu)::value;
-        if (n > kRunsMinSegments)
+        if (direct_runs(n, nwords))
             k_grid_direct<kA8, kEu, true><<<gridDim, kGridBlock, 0, stream>>>(segs, n, dx, dy, dz, grid, counts,
                                                                               w.status);
         else
