@@ -55,12 +55,6 @@
 
 namespace vox {
 
-// Barrier that waits for this wave's LDS traffic only, so global loads
-// issued before it (prefetches) stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Block-wide exclusive sum like block_exclusive_sum, synchronised with
 // lds_barrier so that outstanding global loads are not waited for.
 template <int kBlock>

@@ -9,6 +9,12 @@ namespace vox {
 
 constexpr int kWave = 64;
 
+// Barrier that waits for this wave's LDS traffic only, so global loads
+// issued before it (prefetches) stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // One segment as read from the caller's AoS array: start point and end
 // point.  Loaded with three 8-byte loads when the array is 8-byte aligned
 // (every torch allocation is), else six 4-byte loads.

@@ -8,6 +8,7 @@
 #include "vox_direct.h"
 #include "vox_exact.h"
 #include "vox_internal.h"
+#include "vox_slabs.h"
 
 namespace vox {
 
@@ -43,10 +44,11 @@ __global__ __launch_bounds__(kGridBlock) void k_grid_direct(const int32_t* __res
 constexpr uint32_t kSlabChunk = 8;
 constexpr int kSlabBlock = 1024;
 
-// A wave's segments that may hold voxels of its run (a queue of up to 128),
-// and the windows of the 64 it works on.
+// A wave's segments that may hold voxels of its run (a queue of fewer than 192),
+// and the end points and windows of the 64 it works on.
 struct SlabHits {
-    int32_t seg[6][2 * kWave];
+    uint32_t queue[3 * kWave];
+    int32_t seg[6][kWave];
     uint32_t k0[kWave], len[kWave], pre[kWave];
 };
 
@@ -54,78 +56,257 @@ struct SlabHits {
 // [lo, hi]: [k0, k1], a float estimate of the exact window, never narrower:
 // differences are exact in float, the reciprocal and two products are off by
 // less than 2^-21 of a k inside the segment.
-__device__ __forceinline__ void axis_window_about(int32_t p0, int32_t p1, uint32_t N, int32_t lo, int32_t hi,
-                                                  float& k0, float& k1) {
-    if (p0 == p1) return;
-    const float per = (float)N * __builtin_amdgcn_rcpf((float)(p1 - p0));
-    const float a = ((float)(lo - p0) - 0.5f) * per, b = ((float)(hi - p0) + 0.5f) * per;
-    const float slack = 0.01f + (float)N * 0x1p-20f;
-    k0 = fmaxf(k0, fminf(a, b) - slack);
-    k1 = fminf(k1, fmaxf(a, b) + slack);
+struct AxisSteps {
+    int32_t p0;
+    bool flat;
+    float per, slack;  // samples a voxel
+    __device__ __forceinline__ AxisSteps(int32_t p0_, int32_t p1, uint32_t N)
+        : p0(p0_), flat(p0_ == p1), per((float)N * __builtin_amdgcn_rcpf((float)(p1 - p0_))),
+          slack(0.01f + (float)N * 0x1p-20f) {}
+    __device__ __forceinline__ void clip(int32_t lo, int32_t hi, float& k0, float& k1) const {
+        const float a = ((float)(lo - p0) - 0.5f) * per, b = ((float)(hi - p0) + 0.5f) * per;
+        const float in = lo <= p0 && p0 <= hi ? INFINITY : -INFINITY;  // (the whole axis, or none)
+        k0 = fmaxf(k0, flat ? -in : fminf(a, b) - slack);
+        k1 = fminf(k1, flat ? in : fmaxf(a, b) + slack);
+    }
+};
+
+// A run of the volume's bits: from voxel xlo of row ylo of slab zlo to voxel xhi
+// of row yhi of slab zhi.
+struct SlabBox {
+    int32_t zlo, zhi, ylo, yhi, xlo, xhi;
+    bool one;    // inside one slab
+    bool whole;  // every row of its slabs
+    // Whether a segment's ranges meet it.
+    __device__ __forceinline__ bool meets_y(int32_t ya, int32_t yb, int32_t za, int32_t zb) const {
+        const bool first = (za <= zlo) & (yb >= ylo), last = (zb >= zhi) & (ya <= yhi);
+        return one ? first & last : first | last | ((za < zhi) & (zb > zlo) & (zhi - zlo > 1));
+    }
+    // The segment's samples that may lie in it: from the first to the last of
+    // those in its first slab, its last, and the ones between.
+    __device__ __forceinline__ void window(const AxisSteps& x, const AxisSteps& y, const AxisSteps& z, float n, int32_t dy,
+                                           float& k0, float& k1) const {
+        float a = 0.0f, b = n;
+        z.clip(zlo, zlo, a, b);
+        y.clip(ylo, one ? yhi : dy - 1, a, b);
+        if (one && ylo == yhi) x.clip(xlo, xhi, a, b);
+        k0 = a <= b ? a : INFINITY;
+        k1 = a <= b ? b : -INFINITY;
+        if (one) return;
+        auto also = [&](int32_t z0, int32_t z1, int32_t y1) {
+            float c = 0.0f, d = n;
+            z.clip(z0, z1, c, d);
+            y.clip(0, y1, c, d);
+            k0 = c <= d ? fminf(k0, c) : k0;
+            k1 = c <= d ? fmaxf(k1, d) : k1;
+        };
+        also(zhi, zhi, yhi);
+        if (zhi - zlo > 1) also(zlo + 1, zhi - 1, dy - 1);
+    }
+};
+
+// Whether the runs are cut by the work in them (vox_slabs.h), given as differences
+// in `load`, and then the boundaries w[0], w[1] of workgroup blockIdx.x's run; by
+// one wave.  Every workgroup looks at the same samples and cuts alike.
+__device__ __forceinline__ bool slab_cut(const uint32_t* load, uint32_t runs, uint32_t n, uint32_t samples, uint32_t nwords,
+                                         uint32_t words, uint32_t* w) {
+    const uint32_t lane = __lane_id();
+    static_assert(kSlabMaxRuns == 8 * kWave, "eight runs a lane");
+    uint32_t work[8], before[8], sum = 0, max = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) before[j] = sum += load[8u * lane + j];
+    const uint32_t first = wave_inclusive_sum_dpp(sum) - sum;
+    sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) {
+        work[j] = 8u * lane + j < runs ? first + before[j] : 0u;
+        max = work[j] > max ? work[j] : max;
+        before[j] = sum;
+        sum += work[j];
+    }
+    const uint32_t upto = wave_inclusive_sum_dpp(sum);
+    const uint32_t all = __builtin_amdgcn_readlane(upto, kWave - 1);
+    if (__builtin_amdgcn_ballot_w64(slab_uneven(all, max, runs, n, samples)) == 0) return false;
+    const uint32_t base = slab_base(all, runs), total = runs * base + all;
+    for (uint32_t e = 0; e < 2u; ++e) {
+        const uint32_t r = blockIdx.x + e;
+        if (r == runs) {
+            w[e] = nwords;
+            continue;
+        }
+        const uint32_t target = slab_target(r, runs, total);
+        // The last run that begins at or before it.
+        uint32_t i = 0, start = 0, own = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 8u; ++j) {
+            const uint32_t at = (8u * lane + j) * base + (upto - sum) + before[j];
+            const uint64_t m = __builtin_amdgcn_ballot_w64(8u * lane + j < runs && at <= target);
+            if (m == 0) continue;
+            const uint32_t l = 63u - (uint32_t)__builtin_clzll(m);
+            if (8u * l + j >= i) {
+                i = 8u * l + j;
+                start = __builtin_amdgcn_readlane(at, l);
+                own = __builtin_amdgcn_readlane(work[j], l);
+            }
+        }
+        w[e] = slab_word(target, i, start, base + own, words, nwords);
+    }
+    return true;
 }
 
 // One launch for a whole small call, with no atomics on the volume and no
-// clear pass: workgroup b holds words [b * words, (b + 1) * words) of the volume
-// in LDS, reads every segment, and sets the voxels that fall into its run of
-// bits; then it writes the run once.  A wave tests 64 segments at a time
-// against the run's z (and, for a run inside one z slab, y) range and queues
-// those that may touch it; from a queue of 64 it takes each segment's k-window
-// in that range (every coordinate is monotone in k), cuts the windows into
-// chunks of 8 samples, and its lanes take a chunk each, with one division per
-// axis at its start, testing each voxel against the run.
+// clear pass: every workgroup holds a run of the volume's words in LDS, reads
+// every segment, and sets the voxels that fall into its run of bits; then it
+// writes the run once.  A wave tests 64 segments at a time against the run's z
+// and y ranges and queues those that may touch it; from a queue of 64 it takes
+// each segment's k-window in the run (every coordinate is monotone in k), cuts
+// the windows into chunks of 8 samples, and its lanes take a chunk each, with one
+// division per axis at its start, testing each voxel against the run.
+// The runs are the same number of words each, or cut by the work in them (slab_cut)
+// where the segments lie in few of them: the workgroups begin with the first while
+// one wave of each looks at the estimate, and begin again with the second.
 // Counts: each group of 64 segments by one workgroup.  The status word: by
 // workgroup 0, which sees all segments as the others do.
 //
 // Bound: latency (one launch, the segments from L2, a few divisions a hit).
-// Against the clear and one device atomic a voxel (25 G a second), uniform end
-// points, cleared: 1 000 segments in 256^3 11.3 -> 7.8 us a call, 16 384 there
-// 85 -> 40 us, 16 384 in 512^3 182 -> 50 us.  Windows by exact divisions, and
-// by every lane for its own segment, hit or not: 74 us for 16 384 in 256^3.
+// Against the clear and one device atomic a voxel (25 G a second), cleared, us a
+// call: uniform end points, 1 000 segments in 256^3 7.2 / 11.5, 16 384 there
+// 37 / 85, 16 384 in 512^3 51 / 186; the same in one z slice 10.7 / 20.8,
+// 57 / 250 and 86 / 210 (without the cut 40, 615 and 1175, the work of one
+// workgroup; the estimate costs 0.3 of the 7.2); at most 8 voxels long,
+// 16 384 in 512^3 13.4 / 11.3, and in one slice 18.1 / 11.0 (without the cut 92).
+// Windows by exact divisions, and by every lane for its own segment, hit or not:
+// 74 us for 16 384 uniform ones in 256^3.
 template <bool kAligned8, bool kEuclid>
 __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __restrict__ segs, int32_t n, int32_t dx,
                                                            int32_t dy, int32_t dz, uint32_t* __restrict__ grid,
-                                                           int64_t nwords, uint32_t words, bool clear,
+                                                           uint32_t nwords, uint32_t words, bool clear,
                                                            int32_t* __restrict__ counts,
                                                            int32_t* __restrict__ status) {
     extern __shared__ __align__(16) uint32_t run[];
     __shared__ SlabHits hits[kSlabBlock / kWave];
+    __shared__ uint32_t load[kSlabMaxRuns], bounds_s[2], cut_s;
     __shared__ int32_t bad_s;
-    const uint32_t lane = __lane_id(), wave = threadIdx.x / kWave;
+    const uint32_t lane = __lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     SlabHits& h = hits[wave];
-    const int64_t w0 = (int64_t)blockIdx.x * words;
-    const uint32_t nw = nwords - w0 < (int64_t)words ? (uint32_t)(nwords - w0) : words;
-    const int64_t slab = (int64_t)dx * dy, b0 = w0 * 32;
-    const int64_t total = slab * dz;
-    const int64_t b1 = b0 + (int64_t)nw * 32 < total ? b0 + (int64_t)nw * 32 : total;
-    const uint32_t nbits = (uint32_t)(b1 - b0);
-    // Voxels of the run: z in [zlo, zhi], y in [ylo, yhi].
-    const int32_t zlo = (int32_t)(b0 / slab), zhi = (int32_t)((b1 - 1) / slab);
-    const int32_t ylo = zlo == zhi ? (int32_t)((b0 - zlo * slab) / dx) : 0;
-    const int32_t yhi = zlo == zhi ? (int32_t)((b1 - 1 - zlo * slab) / dx) : dy - 1;
-    for (uint32_t w = threadIdx.x; w < nw; w += kSlabBlock) run[w] = 0u;
-    if (threadIdx.x == 0) bad_s = 0;
-    __syncthreads();
+    auto inside = [&](const Seg& g) {
+        return ((uint32_t)g.p0[0] < (uint32_t)dx) & ((uint32_t)g.p1[0] < (uint32_t)dx) & ((uint32_t)g.p0[1] < (uint32_t)dy) &
+               ((uint32_t)g.p1[1] < (uint32_t)dy) & ((uint32_t)g.p0[2] < (uint32_t)dz) & ((uint32_t)g.p1[2] < (uint32_t)dz);
+    };
+    // The work in each of the runs of `words` words, by a sample a thread of the
+    // last waves (one a SIMD: all others wait for them): its own spread over the
+    // runs from one end point's to the other's.  (Eight neighbours at a time: whole
+    // lines.)
+    const uint32_t samples = (uint32_t)n < kSlabSamples ? (uint32_t)n : kSlabSamples;
+    const uint32_t st = threadIdx.x - (kSlabBlock - kSlabSamples);
+    Seg g = {};
+    if (st < samples)
+        g = load_seg<kAligned8>(segs, (uint32_t)n <= kSlabSamples ? st : st / 8u * (uint32_t)n / (kSlabSamples / 8u) + st % 8u);
+    // The thread's first two segments (beyond the last, that one again).
+    auto load_at = [&](int32_t i) {
+        i += (int32_t)threadIdx.x;
+        return load_seg<kAligned8>(segs, i < n ? i : n - 1);
+    };
+    Seg sa = {}, sb = {};
+    if (n > 0) {
+        sa = load_at(0);
+        sb = load_at(kSlabBlock);
+    }
+    const Seg own = sa;
+    if (threadIdx.x < kSlabMaxRuns) load[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) {
+        bad_s = 0;
+        cut_s = 0u;
+    }
+    // The run's words and, of its voxels, the first and the last.
+    uint32_t w0, nw, nbits;
+    SlabBox box;
+    const uint32_t slab = (uint32_t)dx * (uint32_t)dy;
+    auto take_run = [&](uint32_t from, uint32_t to) {
+        w0 = from;
+        nw = to - from;
+        // (Fewer than 2^28 bits.)
+        const uint32_t bits = slab * (uint32_t)dz, first = w0 * 32u;
+        nbits = nw != 0u ? (first + nw * 32u < bits ? nw * 32u : bits - first) : 0u;
+        const uint32_t last = nw != 0u ? first + nbits - 1u : first;
+        box.zlo = (int32_t)(first / slab);
+        box.ylo = (int32_t)((first - (uint32_t)box.zlo * slab) / (uint32_t)dx);
+        box.xlo = (int32_t)(first - (uint32_t)box.zlo * slab - (uint32_t)box.ylo * (uint32_t)dx);
+        box.zhi = (int32_t)(last / slab);
+        box.yhi = (int32_t)((last - (uint32_t)box.zhi * slab) / (uint32_t)dx);
+        box.xhi = (int32_t)(last - (uint32_t)box.zhi * slab - (uint32_t)box.yhi * (uint32_t)dx);
+        box.one = box.zlo == box.zhi;
+        box.whole = box.ylo == 0 && box.yhi == dy - 1;
+        if (nw == 0u) box.zhi = -1;  // met by none
+        uint4* r4 = reinterpret_cast<uint4*>(run);
+        for (uint32_t u = threadIdx.x; u < (nw + 3u) / 4u; u += kSlabBlock) r4[u] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    {
+        const uint32_t first = blockIdx.x * words;
+        take_run(first, nwords - first < words ? nwords : first + words);
+    }
+    lds_barrier();
+    if (st < samples) {
+        // (Out by one at most, and the same for every workgroup; a segment that is
+        // not inside the volume counts for the runs nearest to it.)
+        const float per = __builtin_amdgcn_rcpf((float)words * 32.0f), last = (float)(gridDim.x - 1u);
+        auto place = [&](const int32_t* p) {
+            const float row = (float)(int32_t)((uint32_t)p[2] * (uint32_t)dy + (uint32_t)p[1]);
+            return fminf(fmaxf((row * (float)dx + (float)p[0]) * per, 0.0f), last);
+        };
+        const float r0 = place(g.p0), r1 = place(g.p1);
+        const uint32_t lo = (uint32_t)fminf(r0, r1), hi = (uint32_t)fmaxf(r0, r1);
+        uint32_t N = 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const uint32_t d = (uint32_t)g.p1[a] - (uint32_t)g.p0[a];
+            const int32_t m = (int32_t)d < 0 ? (int32_t)(0u - d) : (int32_t)d;
+            N = (uint32_t)m > N ? (uint32_t)m : N;
+        }
+        const uint32_t work = slab_work(N, hi - lo + 1u);
+        atomicAdd(&load[lo], work);
+        if (hi + 1u < kSlabMaxRuns) atomicAdd(&load[hi + 1u], 0u - work);
+    }
+    lds_barrier();
+    // One wave looks whether the runs are cut anew; the others begin, and leave
+    // off when they are.
+    if (wave == 0u && slab_cut(load, gridDim.x, (uint32_t)n, samples, nwords, words, bounds_s) && lane == 0)
+        __hip_atomic_store(&cut_s, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    auto cut_anew = [&] { return __hip_atomic_load(&cut_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u; };
 
     auto wave_fence = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    bool first = true;  // the runs are not cut anew, or not yet
     // The voxels of the queue's segments [0, count), count <= 64.
     auto work = [&](uint32_t count) {
         uint32_t k0 = 0, len = 0;
-        if (lane < count) {
-            Seg g;
+        Seg g = {};
+        if (n <= kSlabBlock) {  // a lane of this wave has it
+            const int from = (int)(h.queue[lane] % kWave) << 2;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                g.p0[a] = h.seg[a][lane];
-                g.p1[a] = h.seg[3 + a][lane];
+                g.p0[a] = __builtin_amdgcn_ds_bpermute(from, own.p0[a]);
+                g.p1[a] = __builtin_amdgcn_ds_bpermute(from, own.p1[a]);
             }
-            const uint32_t N = kEuclid ? euclid_length(g) : (uint32_t)seg_length(g);
+        } else if (lane < count) {
+            g = load_seg<kAligned8>(segs, h.queue[lane]);
+        }
+        if (lane < count) {
+            const bool valid = inside(g);
+            if (!valid) g = Seg{};
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                h.seg[a][lane] = g.p0[a];
+                h.seg[3 + a][lane] = g.p1[a];
+            }
+            const uint32_t N = kEuclid ? euclid_length(g) : seg_axes(g).N;
             float ka = 0.0f, kb = (float)N;
-            axis_window_about(g.p0[2], g.p1[2], N, zlo, zhi, ka, kb);
-            if (zlo == zhi) axis_window_about(g.p0[1], g.p1[1], N, ylo, yhi, ka, kb);
-            if (ka <= kb) {
+            box.window(AxisSteps(g.p0[0], g.p1[0], N), AxisSteps(g.p0[1], g.p1[1], N), AxisSteps(g.p0[2], g.p1[2], N), kb, dy, ka,
+                       kb);
+            if (valid && ka <= kb) {
                 k0 = (uint32_t)__builtin_ceilf(ka);
                 const uint32_t k1 = (uint32_t)kb < N ? (uint32_t)kb : N;
                 len = k1 >= k0 ? k1 - k0 + 1u : 0u;
@@ -138,7 +319,7 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
         h.len[lane] = len;
         h.pre[lane] = incl - ch;
         wave_fence();
-        for (uint32_t q0 = 0; q0 < chunks; q0 += kWave) {
+        for (uint32_t q0 = 0; q0 < chunks && !(first && cut_anew()); q0 += kWave) {
             const uint32_t q = q0 + lane;
             if (q >= chunks) continue;
             // The last lane whose first chunk is at most q owns chunk q
@@ -159,7 +340,7 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
             AxisStep st[3] = {};
             if (N) axis_init3(ax.a, ax.neg, N, k, st);
             int32_t stride[3];
-            int64_t at = -b0;
+            int64_t at = -(int64_t)w0 * 32;
             const int32_t full[3] = {1, dx, (int32_t)slab};
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -181,54 +362,65 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
         wave_fence();  // the scratch is rewritten by the wave's next segments
     };
 
-    bool bad = false;
-    uint32_t queued = 0;
-    Seg next = {};
-    if ((int32_t)(wave * kWave + lane) < n) next = load_seg<kAligned8>(segs, wave * kWave + lane);
-    for (int32_t i0 = (int32_t)wave * kWave; i0 < n; i0 += kSlabBlock) {
-        const int32_t i = i0 + (int32_t)lane;
-        const Seg g = next;
-        if (i + kSlabBlock < n) next = load_seg<kAligned8>(segs, i + kSlabBlock);
-        bool hit = false;
-        if (i < n) {
-            bool ok = true;
-            const int32_t dim[3] = {dx, dy, dz};
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                ok &= (g.p0[a] >= 0) & (g.p0[a] < dim[a]) & (g.p1[a] >= 0) & (g.p1[a] < dim[a]);
-            bad |= !ok;
-            if (!kEuclid && counts && (uint32_t)(i0 / kWave) % gridDim.x == blockIdx.x) {
-                const int64_t c = seg_length(g) + 1;
-                counts[i] = (int32_t)(c > 0x7FFFFFFFll ? 0x7FFFFFFFll : c);
-            }
-            const int32_t za = g.p0[2] < g.p1[2] ? g.p0[2] : g.p1[2], zb = g.p0[2] < g.p1[2] ? g.p1[2] : g.p0[2];
-            const int32_t ya = g.p0[1] < g.p1[1] ? g.p0[1] : g.p1[1], yb = g.p0[1] < g.p1[1] ? g.p1[1] : g.p0[1];
-            hit = ok && za <= zhi && zb >= zlo && ya <= yhi && yb >= ylo;
-        }
-        const uint64_t m = __ballot(hit);
-        if (m == 0) continue;
-        if (hit) {
-            const uint32_t at = queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                h.seg[a][at] = g.p0[a];
-                h.seg[3 + a][at] = g.p1[a];
-            }
-        }
-        queued += (uint32_t)__popcll(m);
-        wave_fence();
-        if (queued >= (uint32_t)kWave) {
-            work(kWave);
-            queued -= kWave;
-            if (lane < queued) {
-#pragma unroll
-                for (int a = 0; a < 6; ++a) h.seg[a][lane] = h.seg[a][kWave + lane];
-            }
-            wave_fence();
+    // Counts.
+    if (!kEuclid && counts) {
+        for (int32_t i0 = ((int32_t)wave * (int32_t)gridDim.x + (int32_t)blockIdx.x) * kWave; i0 < n;
+             i0 += kSlabBlock * (int32_t)gridDim.x) {
+            const int32_t i = i0 + (int32_t)lane;
+            if (i >= n) continue;
+            const int64_t c = seg_length(load_seg<kAligned8>(segs, i)) + 1;
+            counts[i] = (int32_t)(c > 0x7FFFFFFFll ? 0x7FFFFFFFll : c);
         }
     }
-    if (queued) work(queued);
+    // Every workgroup tests every segment, so an instruction here is 0.1 us of a
+    // call of 16 384: few of them where no segment of 64 is near the run.
+    bool bad = false;
+    uint32_t queued = 0;
+    auto test = [&](const Seg& g, int32_t i0) {
+        if (blockIdx.x == 0) bad |= !inside(g);
+        const int32_t za = g.p0[2] < g.p1[2] ? g.p0[2] : g.p1[2], zb = g.p0[2] < g.p1[2] ? g.p1[2] : g.p0[2];
+        const bool near = (za <= box.zhi) & (zb >= box.zlo);
+        if (__builtin_amdgcn_ballot_w64(near) == 0) return;
+        const int32_t i = i0 + (int32_t)threadIdx.x;
+        bool hit = near & (i < n);
+        if (!box.whole) {
+            const int32_t ya = g.p0[1] < g.p1[1] ? g.p0[1] : g.p1[1], yb = g.p0[1] < g.p1[1] ? g.p1[1] : g.p0[1];
+            hit &= box.meets_y(ya, yb, za, zb);
+        }
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+        if (hit)
+            h.queue[queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                (uint32_t)i;
+        queued += (uint32_t)__popcll(m);
+    };
+    const int32_t wave0 = (int32_t)wave * kWave;
+    for (;; first = false) {
+        for (int32_t i0 = 0;;) {
+            for (; i0 + wave0 < n && queued < (uint32_t)kWave; i0 += 2 * kSlabBlock) {
+                test(sa, i0);
+                sa = load_at(i0 + 2 * kSlabBlock);
+                test(sb, i0 + kSlabBlock);
+                sb = load_at(i0 + 3 * kSlabBlock);
+            }
+            if (queued == 0 || (first && cut_anew())) break;
+            wave_fence();
+            const uint32_t count = queued < (uint32_t)kWave ? queued : (uint32_t)kWave;
+            work(count);
+            queued -= count;
+            const uint32_t q0 = h.queue[kWave + lane], q1 = h.queue[2 * kWave + lane];
+            wave_fence();
+            h.queue[lane] = q0;
+            h.queue[kWave + lane] = q1;
+            wave_fence();
+        }
+        lds_barrier();
+        if (!first || cut_s == 0u) break;
+        take_run(__builtin_amdgcn_readfirstlane(bounds_s[0]), __builtin_amdgcn_readfirstlane(bounds_s[1]));
+        queued = 0;
+        sa = load_at(0);
+        sb = load_at(kSlabBlock);
+        lds_barrier();
+    }
     if (blockIdx.x == 0 && __ballot(bad) != 0 && lane == 0) atomicOr(&bad_s, kStatusOutOfRange);
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) *status = bad_s;
@@ -245,23 +437,27 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
     }
 }
 
+constexpr int64_t kSlabMaxWords = 16384;
+static_assert(sizeof(SlabHits) * (kSlabBlock / kWave) + (kSlabMaxRuns + 16) * 4 + (size_t)slab_room(kSlabMaxWords) * 4 <= 163840,
+              "the runs fit a workgroup's LDS");
+
 // Words of a workgroup's run: 256 runs, or runs of 64 KiB in larger volumes.
 static int64_t slab_words(int64_t nwords) {
     int64_t w = ((nwords + 255) / 256 + 31) / 32 * 32;
     if (w < 64) w = 64;
-    return w > 16384 ? 16384 : w;
+    return w > kSlabMaxWords ? kSlabMaxWords : w;
 }
 
-// Which calls take the slabs.  Every workgroup reads every segment, about
-// 1 us a thousand (16 384 segments of log-uniform length: 17 us in 256 runs,
-// 20 us in 512; direct 22 and 44 us), so their product is bounded; more than
+// Which calls take the slabs.  Every workgroup reads every segment, 0.3 us a
+// thousand and more (30 000 in 300 x 299 x 187, uniform / at most 8 voxels long:
+// 61 / 17 us, direct 158 / 12; 16 384 in 256^3 38 / 11, direct 85 / 11), so their
+// product is bounded; more than
 // 512 runs (64 KiB each) lose against the direct form (1000 x 700 x 600, 4 000
 // short segments 33 against 28 us), and so do more than some segments in a small
 // volume, whose direct atomics are few and stay in the L2 (96^3, uniform ones:
 // 1 000 6.9 against 8.6 us, 2 000 10.3 / 8.4, 4 000 16.0 / 12.4; of log-uniform
 // length 6.5 / 8.3, 7.2 / 8.3, 8.3 / 8.5).
 constexpr int64_t kSlabMaxTests = int64_t(1) << 23;
-constexpr int64_t kSlabMaxRuns = 512;
 constexpr int64_t kSlabSmallVolume = 65536;  // words
 constexpr int64_t kSlabSmallSegments = 1536;
 
@@ -272,7 +468,7 @@ static bool use_slabs(int64_t n, int32_t dx, int32_t dy, int32_t dz, bool euclid
     if ((int64_t)dx * dy > (int64_t(1) << 28)) return false;
     const int64_t nwords = ((int64_t)dx * dy * dz + 31) / 32, w = slab_words(nwords), runs = (nwords + w - 1) / w;
     if (nwords <= kSlabSmallVolume && n > kSlabSmallSegments) return false;
-    return runs <= kSlabMaxRuns && n * runs <= kSlabMaxTests;
+    return runs <= (int64_t)kSlabMaxRuns && n * runs <= kSlabMaxTests;
 }
 
 template <bool kAligned8, bool kEuclid>
@@ -281,10 +477,11 @@ static hipError_t launch_slabs(const int32_t* segs, int64_t n, int32_t dx, int32
     const int64_t nwords = ((int64_t)dx * dy * dz + 31) / 32, w = slab_words(nwords);
     const unsigned wgs = (unsigned)((nwords + w - 1) / w);
     static const hipError_t attr = hipFuncSetAttribute((const void*)k_grid_slabs<kAligned8, kEuclid>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 16384 * 4);
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                       (int)slab_room(kSlabMaxWords) * 4);
     if (attr != hipSuccess) return attr;
-    k_grid_slabs<kAligned8, kEuclid><<<dim3(wgs), kSlabBlock, (size_t)w * 4, stream>>>(
-        segs, (int32_t)n, dx, dy, dz, grid, nwords, (uint32_t)w, clear, counts, status);
+    k_grid_slabs<kAligned8, kEuclid><<<dim3(wgs), kSlabBlock, (size_t)slab_room((uint32_t)w) * 4, stream>>>(
+        segs, (int32_t)n, dx, dy, dz, grid, (uint32_t)nwords, (uint32_t)w, clear, counts, status);
     return hipGetLastError();
 }
 

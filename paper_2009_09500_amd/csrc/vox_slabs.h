@@ -1,0 +1,69 @@
+// How the small bit-volume calls deal the volume's words to their workgroups
+// (k_grid_slabs, vox_grid.hip).  Host and device, so that a host check runs the
+// code that the kernel runs.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace vox {
+
+// The volume is cut into `runs` runs of `words` words (the last may be shorter).
+// A workgroup's run is one of these as long as the segments are spread over
+// them; where a few runs would do most of the work (a drawing in one z slice is
+// one run's), the runs are cut anew by an estimate of the work: a quarter of the
+// workgroups by where it is, three quarters by words as before, so that none gets
+// more than about 4/3 of the words (the LDS each has).
+constexpr uint32_t kSlabMaxRuns = 512;
+constexpr uint32_t kSlabSamples = 256;  // segments looked at for the estimate
+
+// Room of a workgroup's run: 4/3 of the words, and what rounding adds (a boundary
+// is a multiple of 32 words; a share is up to 1/kSlabMinBase too long); whole
+// 16-byte units.
+constexpr uint32_t kSlabMinBase = 32;
+__host__ __device__ __forceinline__ constexpr uint32_t slab_room(uint32_t words) {
+    return (words + words / 3u + words / kSlabMinBase + 64u) & ~3u;
+}
+
+// Work of a segment of N steps in each of `span` runs, in voxels: a hit costs as
+// much as some 13 (16 384 segments of 239 / 5 voxels in one workgroup: 1.18 / 0.092
+// ms).  N is clamped so that the sums below stay under 2^32.
+__host__ __device__ __forceinline__ uint32_t slab_work(uint32_t N, uint32_t span) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float per = __builtin_amdgcn_rcpf((float)span);
+#else
+    const float per = 1.0f / (float)span;
+#endif
+    return (uint32_t)((float)(N < (1u << 18) ? N : 1u << 18) * per) + 13u;
+}
+
+// What every run weighs for its words alone, and whether the estimate (the runs'
+// work `load`, its sum and maximum, from `samples` of the n segments) asks for a
+// cut by work: a run with more than 16 times the mean, and more of it than
+// some microseconds.  (Uniform end points give 1.5 times the mean, a corner of a
+// quarter of the sides 6; cut at 6 such a corner took 4 000 segments in 256^3 from
+// 14.4 to 17.5 us, since cuts within a slice make every slice two workgroups'.)
+__host__ __device__ __forceinline__ uint32_t slab_base(uint32_t sum, uint32_t runs) {
+    return 3u * ((sum + runs - 1u) / runs);
+}
+__host__ __device__ __forceinline__ bool slab_uneven(uint32_t sum, uint32_t max, uint32_t runs, uint32_t n,
+                                                     uint32_t samples) {
+    // (The last: slab_base(sum, runs) >= kSlabMinBase.)
+    return ((float)max * (float)runs > 16.0f * (float)sum) & ((float)max * (float)n > 8192.0f * (float)samples) &
+           (sum > runs * ((kSlabMinBase + 2u) / 3u - 1u));
+}
+
+// Weight before the r-th of `runs` boundaries, of all runs' weight `total`.
+__host__ __device__ __forceinline__ uint32_t slab_target(uint32_t r, uint32_t runs, uint32_t total) {
+    const uint32_t rest = total % runs;
+    return r * (total / runs) + (r < rest ? r : rest);
+}
+// The boundary's word, in run i, which begins at weight `before` (at most
+// target) and weighs `weight`.
+__host__ __device__ __forceinline__ uint32_t slab_word(uint32_t target, uint32_t i, uint32_t before, uint32_t weight,
+                                                       uint32_t words, uint32_t nwords) {
+    const uint32_t w = i * words + (uint32_t)((uint64_t)(target - before) * words / weight);
+    return (w < nwords ? w : nwords) & ~31u;
+}
+
+}  // namespace vox
