@@ -1075,6 +1075,107 @@ __device__ __forceinline__ uint64_t scan_totals(const WorkView& wv, uint32_t NB,
     return total;
 }
 
+// What split_least asks for: the voxels and pieces of a sample of the segments, one
+// in each of its threads' shares of the rows, and the words of the box that
+// holds it, in every scene.
+constexpr uint32_t kSampleThreads = 256;
+struct SplitSample {
+    uint32_t voxels, pieces;
+    uint64_t words;
+};
+struct SampleSeg {
+    const BrickScene* sc;
+    Seg g;
+    bool any;
+};
+__device__ __forceinline__ SampleSeg sample_load(const TableView& tv) {
+    SampleSeg out{tv.scenes, Seg{}, false};
+    if (threadIdx.x >= kSampleThreads) return out;
+    const uint32_t at = threadIdx.x * tv.h.rows, r = at / kSampleThreads;
+    out.sc = tv.scenes + (tv.row_scene ? tv.row_scene[r] : 0u);
+    int64_t lo, hi;
+    seg_range(out.sc->n, (int)(r - out.sc->row_base), (int)out.sc->rows, lo, hi);
+    lo += (hi - lo) * (int64_t)(at % kSampleThreads) / kSampleThreads;
+    out.any = lo < hi;
+    if (out.any) out.g = load_seg<true>(out.sc->segs, lo);
+    return out;
+}
+
+// The larger halves of the wave's values, in lane 63 (row shifts and broadcasts,
+// as wave_inclusive_sum_dpp).
+__device__ __forceinline__ u16x2 wave_max_dpp(u16x2 v) {
+    auto step = [&](auto ctrl, auto rows) {
+        const u16x2 o = __builtin_bit_cast(u16x2, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
+                                                                             decltype(rows)::value, 0xf, false));
+        v = __builtin_elementwise_max(v, o);
+    };
+    step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+    return v;
+}
+
+// All threads of a block; s: 8 words of LDS.
+__device__ __forceinline__ SplitSample sample_pieces(const SampleSeg& from, uint32_t n_scenes, uint32_t* s) {
+    if (threadIdx.x < 8u) s[threadIdx.x] = 0u;
+    __syncthreads();
+    if (threadIdx.x < kSampleThreads) {
+        const BrickGeom& bg = from.sc->bg;
+        const Seg& g = from.g;
+        uint32_t voxels = 0, pieces = 0;
+        u16x2 box[3] = {};  // largest coordinate, 16383 - the smallest
+        if (from.any && in_volume(g, bg)) {
+            voxels = seg_axes(g).N + 1u;
+            pieces = walk_estimate(g.p0, g.p1, bg.lg);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const int32_t c0 = g.p0[a] < g.p1[a] ? g.p0[a] : g.p1[a], c1 = g.p0[a] < g.p1[a] ? g.p1[a] : g.p0[a];
+                box[a] = (u16x2){(uint16_t)c1, (uint16_t)(16383 - c0)};
+            }
+        }
+        voxels = wave_inclusive_sum_dpp(voxels);
+        pieces = wave_inclusive_sum_dpp(pieces);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) box[a] = wave_max_dpp(box[a]);
+        if (__lane_id() == kWave - 1) {
+            atomicAdd(&s[0], voxels);
+            atomicAdd(&s[1], pieces);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                atomicMax(&s[2 + a], (uint32_t)box[a][0]);
+                atomicMax(&s[5 + a], (uint32_t)box[a][1]);
+            }
+        }
+    }
+    __syncthreads();
+    SplitSample out{s[0], s[1], n_scenes};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const uint32_t largest = s[2 + a], smallest = 16383u - s[5 + a];
+        out.words *= largest > smallest ? largest - smallest + 1u : 1u;
+    }
+    out.words = (out.words + 31u) / 32u;
+    __syncthreads();
+    return out;
+}
+
+// Records from which a brick is cut, by a block that knows the largest brick's.
+// busy(): how many have any.  (It and the sample are taken where a brick would be
+// cut anyway.)
+template <typename Busy>
+__device__ __forceinline__ uint64_t cut_threshold(const TableView& tv, uint64_t total, uint32_t max, uint32_t* s,
+                                                  Busy busy) {
+    const uint64_t most = split_threshold(total);
+    if ((uint64_t)max <= most) return most;
+    const uint32_t bricks = busy();
+    if (bricks > kSplitFewBricks) return most;
+    const SplitSample p = sample_pieces(sample_load(tv), tv.h.n_scenes, s);
+    return split_threshold(total, split_least(total, p.voxels, p.pieces, p.words, bricks));
+}
+
 // The fill's work items (see kSplitShares) when some brick is cut, the same
 // way: item_base[b] = extra items before brick b (a brick of k items has
 // k - 1), the brick of each extra item, the list of cut bricks, and the
@@ -1084,9 +1185,8 @@ __device__ __forceinline__ uint64_t scan_totals(const WorkView& wv, uint32_t NB,
 // items are the bricks (n_split = 0 tells the fill and the scatter so, and
 // the item arrays are not written).
 template <int kBlock>
-__device__ __forceinline__ void make_items(const WorkView& wv, uint32_t NB, uint64_t total, uint64_t* lds,
-                                           uint32_t* st, uint32_t* ob, uint32_t* n_split_s) {
-    const uint64_t T = split_threshold(total);
+__device__ __forceinline__ void make_items(const WorkView& wv, uint32_t NB, uint64_t T, uint64_t* lds, uint32_t* st,
+                                           uint32_t* ob, uint32_t* n_split_s) {
     if (threadIdx.x == 0) *n_split_s = 0u;  // (ordered before the atomics below by the scan's barriers)
     uint64_t extra = 0;
     for (uint32_t c0 = 0; c0 < NB; c0 += kBaseChunk) {
@@ -1181,13 +1281,19 @@ __global__ __launch_bounds__(256) void k_brick_colscan(uint8_t* __restrict__ wor
 __global__ __launch_bounds__(kBaseBlock) void k_brick_base(uint8_t* __restrict__ work, uint64_t work_bytes) {
     __shared__ uint64_t lds[kBaseBlock / kWave];
     __shared__ uint32_t st[kBaseStage], ob[kBaseStage];
-    __shared__ uint32_t n_split_s, max_s;
+    __shared__ uint32_t n_split_s, max_s, sample_s[8];
     const TableView tv = table_view(work + kWorkTable);
     const WorkView wv = work_of(work, tv);
     if (*wv.ok == 0) return;
     const uint64_t total = scan_totals<kBaseBlock>(wv, tv.h.bricks, work_bytes, lds, st, ob, &max_s);
-    if ((uint64_t)max_s > split_threshold(total)) {
-        make_items<kBaseBlock>(wv, tv.h.bricks, total, lds, st, ob, &n_split_s);
+    const uint64_t T = cut_threshold(tv, total, max_s, sample_s, [&] {
+        uint64_t busy = 0, all;
+        for (uint32_t b = threadIdx.x; b < tv.h.bricks; b += kBaseBlock) busy += wv.totals[b] != 0u ? 1u : 0u;
+        (void)block_exclusive_sum<kBaseBlock>(busy, lds, all);
+        return (uint32_t)all;
+    });
+    if ((uint64_t)max_s > T) {
+        make_items<kBaseBlock>(wv, tv.h.bricks, T, lds, st, ob, &n_split_s);
     } else if (threadIdx.x == 0) {
         *wv.n_items = tv.h.bricks;
         *wv.n_split = 0u;
@@ -1308,15 +1414,22 @@ __device__ __forceinline__ void zero_brick(const BrickScene& sc, uint32_t lb) {
         const int32_t e = bg.dim[ax] - org[ax];
         ext[ax] = e < (1 << bg.lg[ax]) ? e : (1 << bg.lg[ax]);
     }
-    // A brick has at most 2^20 bits: 32-bit index arithmetic.
-    const uint32_t xws = (uint32_t)ext[0] >> 5, ey = (uint32_t)ext[1];
-    const uint32_t words = xws * ey * (uint32_t)ext[2];
+    // Over the brick's words by shifts (divisions by the extents took longer than
+    // the stores), 16 bytes at a time where rows are whole such units.
     const int64_t row_words = (int64_t)bg.dim[0] >> 5;
-    for (uint32_t t = threadIdx.x; t < words; t += blockDim.x) {
-        const uint32_t xw = t % xws, r = t / xws;
-        const uint32_t y = r % ey, z = r / ey;
-        sc.grid[((int64_t)(org[2] + (int32_t)z) * bg.dim[1] + (org[1] + (int32_t)y)) * row_words + (org[0] >> 5) +
-                xw] = 0u;
+    uint32_t* grid = sc.grid + ((int64_t)org[2] * bg.dim[1] + org[1]) * row_words + (org[0] >> 5);
+    const bool vec = ((uint32_t)bg.dim[0] & 127u) == 0u;
+    const int lgu = bg.lg[0] - (vec ? 7 : 5);  // units a row
+    const int32_t xus = ext[0] >> (vec ? 7 : 5);
+    for (uint32_t u = threadIdx.x; u < 1u << (lgu + bg.lg[1] + bg.lg[2]); u += blockDim.x) {
+        const int32_t x = (int32_t)(u & ((1u << lgu) - 1u)), r = (int32_t)(u >> lgu);
+        const int32_t y = r & ((1 << bg.lg[1]) - 1), z = r >> bg.lg[1];
+        if (x >= xus || y >= ext[1] || z >= ext[2]) continue;
+        uint32_t* row = grid + ((int64_t)z * bg.dim[1] + y) * row_words;
+        if (vec)
+            reinterpret_cast<uint4*>(row)[x] = make_uint4(0u, 0u, 0u, 0u);
+        else
+            row[x] = 0u;
     }
 }
 
@@ -1343,14 +1456,14 @@ __device__ __forceinline__ void zero_cut_bricks(const TableView& tv, const WorkV
 // 768^3 (169 K) 90 / 79.
 constexpr uint32_t kScanBricks = kHistBlock;    // a thread per brick
 constexpr uint32_t kScanWords = 65536;
-__device__ __forceinline__ bool scan_in_scatter(const BrickScene& sc, const WorkView& wv, uint32_t g,
+__device__ __forceinline__ bool scan_in_scatter(const TableView& tv, const BrickScene& sc, const WorkView& wv, uint32_t g,
                                                 uint64_t work_bytes, uint32_t* cur) {
     __shared__ uint32_t tot[kScanBricks];
     __shared__ uint64_t lds[kHistBlock / kWave];
-    __shared__ uint32_t max_s;
+    __shared__ uint32_t max_s, busy_s, sample_s[8];
     const uint32_t NB = sc.bg.nbricks, G = sc.rows, t = threadIdx.x;
     if (t < NB) tot[t] = cur[t] = 0u;
-    if (t == 0) max_s = 0u;
+    if (t == 0) max_s = busy_s = 0u;
     lds_barrier();
     // Rows c, c + parts, ... of bricks [b, b + per).
     auto sums = [&](auto kPer) {
@@ -1379,13 +1492,16 @@ __device__ __forceinline__ bool scan_in_scatter(const BrickScene& sc, const Work
     lds_barrier();
     const uint32_t mine = t < NB ? tot[t] : 0u;
     atomicMax(&max_s, mine);
+    const uint64_t busy = __builtin_amdgcn_ballot_w64(mine != 0u);
+    if ((t & (kWave - 1)) == 0) atomicAdd(&busy_s, (uint32_t)__popcll(busy));
     uint64_t total;
     const uint64_t base = block_exclusive_sum<kHistBlock>((uint64_t)mine, lds, total);
     if (t < NB) cur[t] += (uint32_t)base;
     const uint64_t cap = work_bytes > wv.rec_off ? (work_bytes - wv.rec_off) / sizeof(Piece) : 0u;
     const bool fits = total <= cap && total < 0xFFFFFFFFull;
-    const uint64_t T = split_threshold(total);
-    const bool cut = (uint64_t)max_s > T;  // (complete: the sum has barriers)
+    // (Both complete: the sum has barriers.  All workgroups take the same sample.)
+    const uint64_t T = cut_threshold(tv, total, max_s, sample_s, [&] { return busy_s; });
+    const bool cut = (uint64_t)max_s > T;
     if (cut && fits && (sc.flags & kSceneClear))
         for (uint32_t i = blockIdx.x; i < NB; i += gridDim.x)
             if ((uint64_t)tot[i] > T) zero_brick(sc, i);
@@ -1432,7 +1548,7 @@ __global__ __launch_bounds__(kHistBlock) void k_brick_scatter(uint8_t* __restric
     const uint32_t g = r - sc.row_base;
     if constexpr (kScan) {
         // (As many workgroups as rows.)
-        if (!scan_in_scatter(sc, wv, r, work_bytes, cur) || r >= tv.h.rows) return;
+        if (!scan_in_scatter(tv, sc, wv, r, work_bytes, cur) || r >= tv.h.rows) return;
     } else {
         const uint32_t* row = wv.hist + sc.hist_off + (size_t)g * NB;
         const uint32_t* base_b = wv.bin_base + sc.brick_base;
@@ -2047,18 +2163,30 @@ void k_brick_fill(uint8_t* __restrict__ work) {
             }
             holds = true;
         } else if (done.split) {
-            const int xws = ext[0] >> 5;  // whole words: dim_x and the brick origin are multiples of 32
-            const int total = rows * xws;
-            for (int t = threadIdx.x; t < total; t += kBlock) {
-                const int xw = t % xws, r = t / xws;
-                const int y = r % ext[1], z = r / ext[1];
-                uint32_t* src = &brick[(((uint32_t)z << LGY) | (uint32_t)y) * (uint32_t)Shape::kBXw + xw];
-                const uint32_t v = *src;
-                *src = 0u;  // zero for the next item
-                if (v != 0u)
-                    __hip_atomic_fetch_or(grid + ((int64_t)(org[2] + z) * bg.dim[1] + (org[1] + y)) * row_words +
-                                              (org[0] >> 5) + xw,
-                                          v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // By shifts, over the rows as wide as the next power of two (words
+            // outside the volume are zero; divisions by the extents took a part some
+            // 20 us), neighbouring lanes neighbouring words (four words a lane: twice
+            // the time where most are set).
+            const int xws = ext[0] >> 5, lgx = xws > 1 ? 32 - __builtin_clz((uint32_t)xws - 1u) : 0;
+            const int total = (ext[2] << LGY) << lgx;
+            uint32_t* dst = grid + ((int64_t)org[2] * bg.dim[1] + org[1]) * row_words + (org[0] >> 5);
+            constexpr int kAtOnce = 8;
+            for (int t = threadIdx.x; t < total; t += kBlock * kAtOnce) {
+                // (Beyond the last word that one again.)
+                uint32_t v[kAtOnce];
+                auto at = [&](int j) { return t + j * kBlock < total ? t + j * kBlock : total - 1; };
+                auto word = [&](int w) { return brick + ((w >> lgx) * Shape::kBXw + (w & ((1 << lgx) - 1))); };
+#pragma unroll
+                for (int j = 0; j < kAtOnce; ++j) v[j] = *word(at(j));
+#pragma unroll
+                for (int j = 0; j < kAtOnce; ++j) {
+                    if (v[j] == 0u) continue;
+                    const int w = at(j), r = w >> lgx;
+                    *word(w) = 0u;  // zero for the next item
+                    __hip_atomic_fetch_or(dst + ((int64_t)(r >> LGY) * bg.dim[1] + (r & ((1 << LGY) - 1))) * row_words +
+                                              (w & ((1 << lgx) - 1)),
+                                          v[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         } else if (whole) {
             // 16-byte units, kUpr per row, rows full width and full slabs:

@@ -300,26 +300,48 @@ __host__ __device__ inline bool brick_geometry(int32_t dx, int32_t dy, int32_t d
 // and a brick can hold far more than a workgroup's fair share of a launch
 // (a small dense volume in a batch is a single brick of millions of
 // voxels), which would leave one workgroup running long after the others.
-// So a brick with more than T records, T = max(kSplitMinRecords,
+// So a brick with more than T records, T = max(split_least,
 // ceil(total / kSplitShares)), becomes ceil(records / T) items, each with
 // an even part of its records, set in LDS by its own workgroup and ORed
 // into the volume with device atomics (the scatter zeroes such a brick
 // first in a cleared volume).  Since every cut brick holds more than
 // T records, the items beyond one per brick number at most
 // total / T <= kSplitShares, and so do the cut bricks.
-// kSplitMinRecords: the flush of a part (a word at a time, atomics) costs
-// about as much as the bits of some thousand short pieces: eight wireframes in
-// 512^3 (0.5 M edges of a few voxels) take 129 us a batch with 4096, 118 with
-// 8192.  kSplitShares: 2048 balances 256 scenes of 64^3 to 512^3 better (1333
+// kSplitShares: 2048 balances 256 scenes of 64^3 to 512^3 better (1333
 // against 1400 us) but cuts more than it pays in others (143 scenes of 64^3 and
 // 128^3: 441 against 426).
 constexpr uint32_t kSplitShares = 1024;
-constexpr uint32_t kSplitMinRecords = 8192;
 constexpr uint32_t kMaxExtraItems = kSplitShares;
 
-__host__ __device__ inline uint64_t split_threshold(uint64_t total) {
+// Records that a part has at least.  A part of T records takes T v ns for its
+// voxels (v a piece), and the parts together cost the flushes: one atomic a word
+// that is not zero, at most w a brick, and as much as some 600 for the rest of a
+// part.  The sum is least at T^2 = 0.28 total (w + 600) / v (0.18 ns a voxel of a
+// workgroup, 0.05 ns a word of the chip where parts meet in the same lines).
+// us a call, with this / 8192 / 4096 records a part: 100 000 segments in a slice of
+// 1024^3 (64 bricks, v = 63, w = 512) 138 / 209 / 146, in a bundle along x there
+// 136 / 233 / 181; 1 M in a 64^3 corner of 512^3 (2 bricks, v = 22, w = 4096) 132 /
+// 130 / 172.  Where half of the chip's workgroups have bricks of their own
+// kSplitMost holds (12 wireframes in 512^3, 4 voxels a piece: 120 us a batch, 131
+// with 4096; 100 000 uniform segments there 70 / 84).
+constexpr uint32_t kSplitLeast = 2048, kSplitMost = 8192;
+constexpr uint32_t kSplitFewBricks = 128;
+__host__ __device__ inline uint32_t split_least(uint64_t total, uint32_t voxels, uint32_t pieces, uint64_t words,
+                                                uint32_t busy_bricks) {
+    if (voxels == 0u || busy_bricks == 0u) return kSplitMost;
+    const float w = (float)words / (float)busy_bricks + 600.0f;
+    const float t2 = 0.28f * (float)total * w * (float)pieces / (float)voxels;
+    const float least = (float)kSplitLeast, most = (float)kSplitMost;
+    if (t2 >= most * most) return kSplitMost;
+    if (t2 <= least * least) return kSplitLeast;
+    uint32_t t = kSplitLeast;  // (the root to a 16th)
+    while ((float)t * (float)t < t2) t += t / 16u;
+    return t < kSplitMost ? t : kSplitMost;
+}
+
+__host__ __device__ inline uint64_t split_threshold(uint64_t total, uint32_t least = kSplitMost) {
     const uint64_t t = total / kSplitShares + (total % kSplitShares != 0u ? 1u : 0u);
-    return t > kSplitMinRecords ? t : kSplitMinRecords;
+    return t > least ? t : least;
 }
 __host__ __device__ inline uint32_t brick_items(uint32_t records, uint64_t T) {
     if (records <= T) return 1u;               // every brick when T >= 2^32
