@@ -1262,17 +1262,27 @@ static void launch_euclid_counts(const int32_t* segs, int64_t n, bool aligned8, 
         euclid_counts<64>(segs, n, aligned8, w.counts, stream);
 }
 
-constexpr int64_t kWalkInCountSegs = 1048576;
+// With one lane a segment the count kernel may walk the segments itself, one launch
+// fewer, but four a thread, a wave as long as its longest.  us a call, walking /
+// not: 400 000 segments of 4 voxels 27 / 27, of 40 at 500 000 68 / 65, 1.3 M 131 /
+// 129, 2 M 178 / 187, 4 M 334 / 355; of 64 to 110 at 1.3 M 195 / 190, 2 M 271 / 277;
+// of 1 to 400 mixed at 1.3 M 377 / 326, 2 M 479 / 472; 100 000 of 1 to 960 209 / 105.
+// A call that asks for the total alone says nothing of the lengths: of 4 at 65 536
+// 22 / 23, 1 M 33 / 38, 2 M 45 / 53, but of 1 to 900 166 / 66 at 65 536, of 1 to 400
+// 110 / 97 at 1 M and 171 / 161 at 2 M.
+constexpr int64_t kWalkVoxels = 32;                     // a segment, by the capacity
+constexpr int64_t kWalkManyVoxels = 64, kWalkManySegs = int64_t(1) << 21;
+
+static bool walk_in_count(int64_t n, const ListWork& w) {
+    if (n == 0 || euclid_count_lanes(n, w) != 1) return false;
+    const int64_t room = w.ntiles * kListTile;
+    if (room == 0) return n >= kWalkManySegs;
+    return room <= kWalkVoxels * n || (n >= kWalkManySegs && room <= kWalkManyVoxels * n);
+}
 
 template <int kKind>
 static void list_count(const int32_t* segs, int64_t n, bool aligned8, const ListWork& w, hipStream_t stream) {
-    // With one lane a segment the count kernel may walk the segments itself, one
-    // launch fewer, but four a thread: where that still fills the chip (1 M
-    // segments of 64 samples 0.146 against 0.150 ms a call), or for short ones.
-    // 100 000 segments of 1 to 960 samples, whose waves walk as long as their
-    // longest: 0.209 against 0.105 ms a call.
-    const bool one_lane = kKind == kListEuclid && n > 0 && euclid_count_lanes(n, w) == 1;
-    const int walk = one_lane && (n >= kWalkInCountSegs || w.ntiles * kListTile <= 32 * n) ? 1 : 0;
+    const int walk = kKind == kListEuclid && walk_in_count(n, w) ? 1 : 0;
     if (kKind == kListEuclid && n > 0 && !walk) launch_euclid_counts(segs, n, aligned8, w, stream);
     // n == 0: one block that writes a zero sum and no flag.
     dim3 grid(n == 0 ? 1u : (unsigned)w.nb);
