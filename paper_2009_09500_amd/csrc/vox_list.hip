@@ -1434,9 +1434,11 @@ static void list_voxels_euclid(const int32_t* segs, int64_t n, bool aligned8, co
                                const ListWork& w, int16_t* voxels, hipStream_t stream) {
     // (Waves in all, by the voxels a segment: short ones gain more from sharing.
     // 2048 / 4096 / 8192: 30 000 segments of 20 samples 18.2 / 19.2 / 22.6 us a
-    // call, 20 000 of 50 21.3 / 20.2 / 23.2, 48 000 of 1 to 2048 115 / 88 / 84.)
+    // call, 20 000 of 50 21.3 / 20.2 / 23.2, 48 000 of 1 to 2048 115 / 88 / 84.
+    // 4096 / 8192: 20 000 of 64 20.2 / 23.2, of 120 23.5 / 25.4, 65 000 of 120 38.8 /
+    // 38.3, 50 000 of 300 52 / 49.)
     const int64_t avg = w.ntiles * kListTile / n;
-    int64_t per = n / (avg <= 32 ? 2048 : (avg <= 64 ? 4096 : 8192));
+    int64_t per = n / (avg <= 32 ? 2048 : (avg <= 128 ? 4096 : 8192));
     per = per < 1 ? 1 : (per > kWave ? kWave : per);
     const int64_t segs_per_block = per * (kCountBlock / kWave);
     int64_t blocks = (n + segs_per_block - 1) / segs_per_block;
