@@ -196,7 +196,8 @@ __device__ __forceinline__ int32_t list_status(int32_t flags, int64_t total, int
 // samples that start a new voxel) and their block sums; out-of-range flags
 // (int16 lists: a coordinate outside int16; int32 lists: an axis spanning
 // 2^30 or more), and whether a segment is longer than kFix16MaxN.
-// (64 VGPRs at most, so that two blocks of 1024 run on a CU.)
+// (64 VGPRs at most, so that two blocks of 1024 run on a CU where there are more
+// blocks than CUs, above a million segments.)
 template <bool kAligned8, int kKind, int kBlock>
 __global__ __launch_bounds__(kBlock, kBlock == 1024 ? 8 : 1) void k_list_count(const int32_t* __restrict__ segs,
                                                        int64_t n, uint32_t* __restrict__ counts,
@@ -273,10 +274,12 @@ __global__ __launch_bounds__(kScanBlock) void k_list_scan(int64_t* __restrict__ 
 
 // --------------------------------------------------- offsets and tile map
 
-// Segments from which the count and offsets kernels take 4096 a block of 1024
-// threads rather than 1024 a block of 256.
-constexpr int64_t kLargeBlockSegs = 262144;
-constexpr int kLargeBlock = 1024;
+// Threads of a block of the count and offsets kernels, four segments each: as few
+// as leave at most kFusedScanMaxBlocks blocks (300 000 segments of 4 voxels 18.7 us
+// a call in blocks of 512, 21.3 of 1024).
+constexpr int kMidBlock = 512, kLargeBlock = 1024;
+constexpr int64_t kSmallBlockSegs = 262144, kMidBlockSegs = 524288;
+static int count_block(int64_t n) { return n <= kSmallBlockSegs ? kCountBlock : n <= kMidBlockSegs ? kMidBlock : kLargeBlock; }
 
 // Count blocks up to this many: the offsets kernel sums the count blocks'
 // partials itself (every block reads all of them, 12 bytes each) and the
@@ -419,7 +422,9 @@ __global__ __launch_bounds__(kCountBlock) void k_list_one_block(
                                         total);
 }
 
-static_assert(kLargeBlockSegs <= kFusedScanMaxBlocks * kSegsPerCountBlock, "small blocks are always fused");
+static_assert(kSmallBlockSegs <= kFusedScanMaxBlocks * kSegsPerCountBlock &&
+                  kMidBlockSegs <= kFusedScanMaxBlocks * kMidBlock * kCountPerThread,
+              "smaller blocks are always fused");
 
 // ------------------------------------------------------------ voxel tiles
 
@@ -1222,7 +1227,8 @@ ListWork list_workspace(void* d_work, int64_t n, int64_t capacity) {
     w.counts = reinterpret_cast<uint32_t*>(p);
     p += align_up((size_t)(n > 0 ? n : 1) * sizeof(uint32_t));
     w.tile_seg = reinterpret_cast<int32_t*>(p);
-    w.nb = n > kLargeBlockSegs ? (n + kLargeBlock * kCountPerThread - 1) / (kLargeBlock * kCountPerThread) : nb;
+    const int64_t per = (int64_t)count_block(n) * kCountPerThread;
+    w.nb = n > 0 ? (n + per - 1) / per : 1;
     w.ntiles = (capacity + kListTile - 1) / kListTile;
     return w;
 }
@@ -1295,8 +1301,10 @@ static void list_count(const int32_t* segs, int64_t n, bool aligned8, const List
             k_list_count<false, kKind, kBlock><<<grid, kBlock, 0, stream>>>(segs, n, w.counts, w.block_sums,
                                                                             w.block_flags, walk);
     };
-    if (n > kLargeBlockSegs)
+    if (count_block(n) == kLargeBlock)
         launch(std::integral_constant<int, kLargeBlock>{});
+    else if (count_block(n) == kMidBlock)
+        launch(std::integral_constant<int, kMidBlock>{});
     else
         launch(std::integral_constant<int, kCountBlock>{});
 }
@@ -1369,8 +1377,10 @@ hipError_t launch_list_offsets(int64_t n, int64_t* offsets, const ListWork& w, i
             n, w.counts, w.block_sums, w.block_flags, w.nb, capacity, offsets, w.tile_seg, mapped, w.total, w.status,
             w.host);
     };
-    if (n <= kLargeBlockSegs)
+    if (count_block(n) == kCountBlock)
         launch(std::true_type{}, std::integral_constant<int, kCountBlock>{});
+    else if (count_block(n) == kMidBlock)
+        launch(std::true_type{}, std::integral_constant<int, kMidBlock>{});
     else if (w.nb <= kFusedScanMaxBlocks)
         launch(std::true_type{}, std::integral_constant<int, kLargeBlock>{});
     else
