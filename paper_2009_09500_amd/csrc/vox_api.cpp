@@ -2,7 +2,6 @@
 // carving and the launch sequence of each call.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -12,6 +11,7 @@
 
 #include "vox.h"
 #include "vox_internal.h"
+#include "vox_slots.h"
 
 namespace {
 
@@ -122,53 +122,44 @@ namespace {
 
 // Pinned host memory in which a call finds its status and total after the
 // synchronisation, written by the kernel that computes them: a copy from the
-// workspace costs 10 us more.  One page for the process, allocated by the first
-// call that asks for a total; a call takes a slot of its own for as long as it
-// lasts, and copies when none is free.
-class HostSlots {
-  public:
-    struct Slot {
-        int64_t status, total, pad[6];
-    };
-    Slot* take(bool may_allocate) {
-        Slot* page = page_.load(std::memory_order_acquire);
-        if (page == nullptr && may_allocate) page = allocate();
-        if (page == nullptr) return nullptr;
-        uint64_t used = used_.load(std::memory_order_relaxed);
-        while (used != ~uint64_t(0)) {
-            const int i = __builtin_ctzll(~used);
-            if (used_.compare_exchange_weak(used, used | uint64_t(1) << i, std::memory_order_acquire)) return page + i;
-        }
+// workspace costs 10 us more.
+vox::HostSlots::Slot* allocate_slots() {
+    // (Another thread may be capturing a graph: not a part of it.)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+    void* p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, vox::HostSlots::kSlots * sizeof(vox::HostSlots::Slot),
+                                       hipHostMallocPortable | hipHostMallocMapped);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) return static_cast<vox::HostSlots::Slot*>(p);
+    (void)hipGetLastError();
+    return nullptr;
+}
+vox::HostSlots g_slots(allocate_slots);
+
+// A slot for a call on stream s, and its device address; none on a stream that is
+// being captured, where the call will be refused, or when its address cannot be
+// had.
+vox::HostSlots::Slot* take_slot(hipStream_t s, bool may_allocate, int64_t*& device) {
+    device = nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+        (void)hipGetLastError();
         return nullptr;
     }
-    void give_back(Slot* s) {
-        used_.fetch_and(~(uint64_t(1) << (s - page_.load(std::memory_order_relaxed))), std::memory_order_release);
+    if (capture != hipStreamCaptureStatusNone) return nullptr;
+    vox::HostSlots::Slot* slot = g_slots.take(may_allocate);
+    void* mapped = nullptr;
+    if (slot && hipHostGetDevicePointer(&mapped, slot, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        g_slots.give_back(slot);
+        slot = nullptr;
     }
+    device = static_cast<int64_t*>(mapped);
+    return slot;
+}
 
-  private:
-    Slot* allocate() {
-        std::lock_guard<std::mutex> lk(mu_);
-        if (tried_) return page_.load(std::memory_order_relaxed);
-        tried_ = true;
-        // (Another thread may be capturing a graph: not a part of it.)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
-        void* p = nullptr;
-        const hipError_t e = hipHostMalloc(&p, 64 * sizeof(Slot), hipHostMallocPortable | hipHostMallocMapped);
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        page_.store(static_cast<Slot*>(p), std::memory_order_release);
-        return static_cast<Slot*>(p);
-    }
-    std::atomic<Slot*> page_{nullptr};
-    std::atomic<uint64_t> used_{0};
-    std::mutex mu_;
-    bool tried_ = false;
-};
-HostSlots g_slots;
+bool stream_idle(void* stream) { return hipStreamSynchronize(static_cast<hipStream_t>(stream)) == hipSuccess; }
 
 }  // namespace
 
@@ -198,13 +189,7 @@ int vox::segments_to_list(const void* d_segs, int64_t n, int64_t* d_offsets, voi
     const bool a8 = aligned(d_segs, 8);
     vox::ListWork w = vox::list_workspace(d_work, n, cap);
     hipError_t e;
-    HostSlots::Slot* slot = h_total ? g_slots.take(may_allocate) : nullptr;
-    void* mapped = nullptr;
-    if (slot && hipHostGetDevicePointer(&mapped, slot, 0) != hipSuccess) {
-        g_slots.give_back(slot);
-        slot = nullptr;
-    }
-    w.host = static_cast<int64_t*>(mapped);
+    SlotUse slot(g_slots, h_total ? take_slot(s, may_allocate, w.host) : nullptr, stream_idle, stream);
     const bool at_once = want && !euclid && vox::list_one_launch(n, cap);
     if (at_once) {
         // (The kernel itself checks the header before it writes a voxel.)
@@ -232,12 +217,11 @@ int vox::segments_to_list(const void* d_segs, int64_t n, int64_t* d_offsets, voi
         int64_t hdr[2];
         if (!slot && (e = hipMemcpyAsync(hdr, d_work, sizeof(hdr), hipMemcpyDeviceToHost, s)) != hipSuccess)
             return device_fail(e, "read total");
-        // (After an error the slot stays taken: a kernel may still write it.)
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return device_fail(e, "synchronize");
         if (slot) {
             hdr[0] = __atomic_load_n(&slot->status, __ATOMIC_RELAXED);
             hdr[1] = __atomic_load_n(&slot->total, __ATOMIC_RELAXED);
-            g_slots.give_back(slot);
+            slot.done();
         }
         const int32_t st = (int32_t)(hdr[0] & 0xFFFFFFFF);
         *h_total = hdr[1];
