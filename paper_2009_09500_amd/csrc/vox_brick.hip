@@ -1688,9 +1688,7 @@ struct StepCheb {
 // same bit again.  The record holds integers, so a chunk starts with one
 // division per axis at k = klo + koff (numerators below 2^31); the quotients
 // move the bit index from the segment's start point, mod the brick's voxel
-// count.  Fractions and slopes of 32 bits from the reciprocal, biased
-// upwards by 2048 units (the float error is below 1024): at most 3072 units
-// too large each, below 32 x 3072 < 2^32 / 2N after a chunk's 31 steps.
+// count.  Fractions and slopes of 32 bits from the reciprocal (fix32_about).
 struct StepEuclid {
     uint32_t f[3], d[3];
     int32_t idx, s[3];
@@ -1713,8 +1711,8 @@ struct StepEuclid {
             uint32_t q, r;
             divmod_down(__umul24(k, two_a[i]) + (two_n >> 1) - neg, two_n, rcpd, q, r);
             const bool tie = two_a[i] >= two_n;  // moves at every step
-            f[i] = tie ? 0x80000000u : (uint32_t)((float)r * scale) + 2048u;
-            d[i] = tie ? 0xFFFFFFFFu : (uint32_t)((float)two_a[i] * scale) + 2048u;
+            f[i] = tie ? 0x80000000u : fix32_about(r, scale);
+            d[i] = tie ? 0xFFFFFFFFu : fix32_about(two_a[i], scale);
             idx += __mul24((int32_t)q, s[i]);
         }
     }

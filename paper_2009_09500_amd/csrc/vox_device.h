@@ -167,6 +167,38 @@ __host__ __device__ __forceinline__ uint32_t fix23_fraction(uint32_t r, uint32_t
     return two_a < two_n ? f : 1u << 22;
 }
 
+// Axes under the Euclidean N of eq. (1), where a <= N, as 32-bit fractions: an axis
+// moves at a step exactly when fraction and slope carry.
+//
+// From a remainder r < 2N, and 2a < 2N as its step (lists, whole walks, N <=
+// 32767): both rounded up, by less than 1.2 units, so after N steps the sum is less
+// than 1.2 (N + 1) <= 2^32 / 2N units too large, and values are multiples of 1 / 2N.
+// unit: 2^32 / 2N.
+__host__ __device__ __forceinline__ uint32_t fix32_of(uint32_t x, double unit) {
+    return (uint32_t)__builtin_ceil((double)x * unit + 0.125);
+}
+// From the segment (lists, N <= 32767): at sample k the axis has moved the high word
+// of fix32_at(k), whose low word is its fraction, in the direction of its sign.  An
+// axis with a = N moves at every step: a slope of 1 - 2^-32 from a start of 1/2.
+constexpr uint32_t kFix32Always = ~0u;
+__host__ __device__ __forceinline__ uint32_t fix32_slope(uint32_t a, uint32_t N, double rcp_n) {
+    return a == N ? kFix32Always : (uint32_t)__builtin_ceil((double)a * 0x1p32 * rcp_n + 0.125);
+}
+// Start of an axis with a negative direction, 1/2 - 1/2N (others 1/2).
+__host__ __device__ __forceinline__ uint32_t fix32_start(double rcp_n) {
+    return 0x80000000u - (uint32_t)(0x1p31 * rcp_n);
+}
+__host__ __device__ __forceinline__ uint64_t fix32_at(uint32_t k, uint32_t slope, bool neg, uint32_t start) {
+    return (uint64_t)k * slope + (neg && slope != kFix32Always ? start : 0x80000000u);
+}
+// From a remainder, in float (pieces, N <= 16384, chunks of 32 samples): scale is
+// 2^32 times a reciprocal of 2N within one ulp; biased upwards by 2048 units, more
+// than the error of less than 1024, so at most 3072 units too large each, below
+// 32 x 3072 < 2^32 / 2N after a chunk's 31 steps.
+__host__ __device__ __forceinline__ uint32_t fix32_about(uint32_t x, float scale) {
+    return (uint32_t)((float)x * scale) + 2048u;
+}
+
 // int16 coordinates of eq. (3) in 16.16 fixed point, for N <= kFix16MaxN: the
 // high half of P + k d / N, P = p0 + 1/2, is the voxel's coordinate
 // p0 + floor((2 k d + N) / 2N) as long as the sum is never below its value and

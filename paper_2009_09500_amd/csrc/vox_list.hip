@@ -43,9 +43,7 @@ __device__ __forceinline__ uint32_t list_euclid_length(const Seg& s) {
 // remainders (one division unless k0 = 0), then one step a sample.
 //
 // Up to N = 32767 an axis is a 32-bit fraction f and a slope d, and moves at a
-// step exactly when f + d carries: the remainder over 2N and a / N in 2^-32,
-// each rounded up by less than 1.2 units, so that after all N steps the sum is
-// less than 1.2 (N + 2) < 2^32 / 2N units too large.  A step is three adds with
+// step exactly when f + d carries (fix32_of).  A step is three adds with
 // carry and one add of the (or-ed) carries.  An axis with a = N moves at every
 // step, and then so does the sample.  Longer segments step their remainders.
 template <bool kFromStart>
@@ -79,8 +77,8 @@ __device__ __forceinline__ uint32_t euclid_walk(const Seg& g, uint32_t N, uint32
         uint32_t f[3], d[3];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            f[ax] = (uint32_t)__builtin_ceil((double)r[ax] * unit + 0.125);
-            d[ax] = (uint32_t)__builtin_ceil((double)ta[ax] * unit + 0.125);
+            f[ax] = fix32_of(r[ax], unit);
+            d[ax] = fix32_of(ta[ax], unit);
         }
         auto step = [&] {
             const bool a = __builtin_uadd_overflow(f[0], d[0], &f[0]);
@@ -933,10 +931,7 @@ __device__ __forceinline__ uint32_t euclid_voxels_any(const Seg& g, int16_t* out
 // sample, and 0.196 ms for 1 M segments of 64 samples; this one 0.131 ms, and
 // 0.177 against 0.323 ms for 11 M segments of 5 samples.)
 //
-// Exact: start and slope are rounded up by less than 1.2 units of 2^-32, so at
-// sample k the sum is less than 1.2 (N + 1) <= 2^32 / 2N units too large, and
-// its values are multiples of 1 / 2N.  An axis with a = N, which moves at every
-// step, takes the slope 1 - 2^-32 from a start of 1/2.
+// (Exact: fix32_slope, fix32_at.)
 //
 // The wave's output is contiguous: rows go through an LDS buffer, x and y apart
 // from z (rows of 6 bytes would take unaligned writes, five times as slow), and
@@ -1050,8 +1045,7 @@ struct EuclidLists {
         for (int a = 0; a < 3; ++a) {
             const bool neg = ((e.n_neg >> (24 + a)) & 1u) != 0u;
             mk[a] = neg ? ~0u : 0u;
-            const uint64_t t = (uint64_t)k0 * e.slope[a] +
-                               (neg && e.slope[a] != ~0u ? e.start : 0x80000000u);
+            const uint64_t t = fix32_at(k0, e.slope[a], neg, e.start);
             c[a] = e.c[a] + (uint32_t)(t >> 32);
             f[a] = g[a] = (uint32_t)t;
             kept |= f[a] < e.slope[a];  // the step to k0 carried
@@ -1139,10 +1133,10 @@ struct EuclidLists {
             const int32_t d = g.p1[a] - g.p0[a];
             const uint32_t len = (uint32_t)(d < 0 ? -d : d);
             e.c[a] = (uint32_t)g.p0[a] ^ (d < 0 ? ~0u : 0u);
-            e.slope[a] = len == N ? ~0u : (uint32_t)__builtin_ceil((double)len * 0x1p32 * rcp_n + 0.125);
+            e.slope[a] = fix32_slope(len, N, rcp_n);
             e.n_neg |= d < 0 ? 1u << (24 + a) : 0u;
         }
-        e.start = 0x80000000u - (uint32_t)(0x1p31 * rcp_n);
+        e.start = fix32_start(rcp_n);
         w.seg[lane] = e;
         fence();
         // Lanes a segment: the fewest passes over the wave's segments, those
