@@ -112,7 +112,7 @@ __host__ __device__ constexpr uint64_t up256(uint64_t v) { return (v + 255u) & ~
 // (k = klo), made by the scatter, which has the segment at hand, so that the
 // fill only unpacks it and never gathers segments.  Minor axes a < b in axis
 // order, m the dominant axis (the first of the longest ones), fractions and
-// slopes of the minor axes in 23 bits (fix23_axis):
+// slopes of the minor axes in 23 bits (fix23_fraction, fix23_slope):
 //   e  fraction of a << 9 | slope of b, bits 0-8
 //   t  fraction of b << 9 | slope of b, bits 9-17
 //   v  slope of a << 9 | negm << 5 | slope of b, bits 18-22
@@ -334,7 +334,7 @@ __device__ __forceinline__ uint32_t xcd_row(uint32_t w, uint32_t G) {
 // The table header, status word, flags and work queues of a launch whose
 // scenes have been numbered (one lane).
 __device__ __forceinline__ void write_table(uint8_t* work, const BrickLaunch& L, uint64_t work_bytes, uint32_t rows_c,
-                                            uint32_t bricks_c, uint32_t direct_c, uint32_t max_nb, uint64_t hist_c,
+                                            uint32_t bricks_c, uint32_t direct_c, uint64_t hist_c,
                                             uint64_t segs_c, uint64_t dsegs_c, bool bad) {
     uint8_t* tb = work + kWorkTable;
     BrickTable t{};
@@ -343,7 +343,6 @@ __device__ __forceinline__ void write_table(uint8_t* work, const BrickLaunch& L,
     t.rows = rows_c;
     t.bricks = bricks_c;
     for (int a = 0; a < 3; ++a) t.lg[a] = L.lg[a];
-    t.max_nb = max_nb;
     t.hist_words = hist_c;
     t.data_off = kWorkTable + L.table_bytes;
     t.n_direct = direct_c;
@@ -377,14 +376,11 @@ __global__ __launch_bounds__(kBlock) void k_brick_plan(const vox_scene* __restri
                                                            uint8_t* __restrict__ work, uint64_t work_bytes) {
     __shared__ uint32_t scan32[kBlock / kWave];
     __shared__ uint64_t scan64[kBlock / kWave];
-    __shared__ uint32_t bad_s, max_nb_s;
+    __shared__ uint32_t bad_s;
     uint8_t* tb = work + kWorkTable;
     BrickScene* out = reinterpret_cast<BrickScene*>(tb + kTableScenes);
     uint32_t* direct = reinterpret_cast<uint32_t*>(out + L.n_scenes);
-    if (threadIdx.x == 0) {
-        bad_s = 0;
-        max_nb_s = 0;
-    }
+    if (threadIdx.x == 0) bad_s = 0;
     __syncthreads();
     uint32_t rows_c = 0, bricks_c = 0, direct_c = 0;
     uint64_t hist_c = 0, segs_c = 0, dsegs_c = 0;
@@ -404,7 +400,6 @@ __global__ __launch_bounds__(kBlock) void k_brick_plan(const vox_scene* __restri
             nb = isd ? 0u : (b.bg.nbricks + 1u) & ~1u;
             hist = (uint64_t)rows * b.bg.nbricks;
             n = b.n > 0 ? (uint64_t)b.n : 0u;
-            atomicMax(&max_nb_s, b.bg.nbricks);
         }
         uint32_t t_rows, t_nb, t_d;
         uint64_t t_hist, t_n, t_dn;
@@ -430,7 +425,7 @@ __global__ __launch_bounds__(kBlock) void k_brick_plan(const vox_scene* __restri
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    write_table(work, L, work_bytes, rows_c, bricks_c, direct_c, max_nb_s, hist_c, segs_c, dsegs_c, bad_s != 0);
+    write_table(work, L, work_bytes, rows_c, bricks_c, direct_c, hist_c, segs_c, dsegs_c, bad_s != 0);
 }
 
 // The scene of histogram row r of a batch: the last one whose rows start at or
@@ -966,7 +961,7 @@ __global__ __launch_bounds__(kHistBlock) void k_brick_plan_hist(vox_scene one, B
         BrickScene* out = reinterpret_cast<BrickScene*>(work + kWorkTable + kTableScenes);
         out[0] = sc;
         if (isd) reinterpret_cast<uint32_t*>(out + 1)[0] = 0u;
-        write_table(work, L, work_bytes, sc.rows, nb, isd ? 1u : 0u, nb, hist_c, n, isd ? n : 0u, !valid);
+        write_table(work, L, work_bytes, sc.rows, nb, isd ? 1u : 0u, hist_c, n, isd ? n : 0u, !valid);
     }
     // The same decision as the ok word written above.
     const WorkView wv = work_view(work, kWorkTable + L.table_bytes, hist_c, nb);
@@ -1646,7 +1641,7 @@ __device__ __forceinline__ void make_strides(int4* strides) {
 
 // Stepping state of a chunk: samples koff ... of the record's piece.  Per
 // minor axis a 32-bit fraction f and its slope d: the axis advances at a step
-// exactly when f + d carries out of 32 bits (fix23_axis, the 23-bit fractions
+// exactly when f + d carries out of 32 bits (fix23_fraction, the 23-bit fractions
 // moved to the top).  A step is five VALU instructions (two adds with carry,
 // two selects of a stride, one three-way add of the bit index) and three for
 // the LDS word and the bit.  Moving on to a chunk's first sample is a
@@ -1959,7 +1954,7 @@ struct RoundQueue {
 
 // Persistent fill.  Workgroups take work items (a brick, or part of a cut
 // brick) from the work queues (work stealing: bricks differ a lot in work).
-// The item's pieces are listed as chunks of equal lengths (list_chunks) and
+// The item's pieces are listed as chunks of equal lengths (ChunkList) and
 // the waves take rounds of 64 of them from that one list, so that they finish
 // a brick together; each lane reads its chunk's record from the L2.  While
 // an item's rounds run, the next item is claimed and its records' lengths are
@@ -2286,7 +2281,8 @@ void k_brick_fill(uint8_t* __restrict__ work) {
 constexpr int kDirectBlock = 256;
 
 // The segments of the direct scenes, one device atomic per voxel
-// (direct_segments, vox_direct.h).
+// (direct_segments, vox_direct.h; the merge of neighbouring bits that plain calls
+// of many segments take has not been measured here).
 __global__ __launch_bounds__(kDirectBlock) void k_batch_direct(uint8_t* __restrict__ work) {
     const TableView tv = table_view(work + kWorkTable);
     uint32_t nd;

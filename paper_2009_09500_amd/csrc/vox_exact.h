@@ -43,7 +43,9 @@ __host__ __device__ __forceinline__ float rcp_walk(uint32_t y) {
 constexpr uint32_t kNever = 0xFFFFFFFFu;
 
 // First k at which the offset q(k) along an axis reaches m (m >= 1), or
-// kNever if it never does (m > a).  a >= 1 when m <= a.
+// kNever if it never does (m > a).  a >= 1 when m <= a.  (div_ceil_u64, k_reach,
+// axis_window and box_window state what the walk's reciprocals compute, for the
+// host check that compares the two.)
 __host__ __device__ __forceinline__ uint32_t k_reach(uint32_t m, uint32_t a, uint32_t N, uint32_t neg) {
     if (m > a) return kNever;
     // Dominant axis: q(k) = k exactly.
@@ -109,9 +111,6 @@ __host__ __device__ __forceinline__ void cross_advance(AxisCross& c, bool hit) {
     c.kn = hit ? kn : c.kn;
     c.sl = hit ? sl : c.sl;
 }
-
-// Advances an axis whose crossing c.kn has just happened.
-__host__ __device__ __forceinline__ void cross_step(AxisCross& c) { cross_advance(c, true); }
 
 struct SegAxes {
     int32_t p0[3];

@@ -152,7 +152,6 @@ struct BrickTable {
     uint32_t rows;         // histogram rows of all brick scenes
     uint32_t bricks;       // bricks of all brick scenes
     int32_t lg[3];
-    uint32_t max_nb;       // largest per-scene brick count
     uint64_t hist_words;
     uint64_t data_off;     // workspace offset of the histograms (then totals, offsets, records)
     uint32_t n_direct;     // scenes served by the direct kernels
