@@ -2165,16 +2165,16 @@ void k_brick_fill(uint8_t* __restrict__ work) {
             uint32_t* dst = grid + ((int64_t)org[2] * bg.dim[1] + org[1]) * row_words + (org[0] >> 5);
             constexpr int kAtOnce = 8;
             for (int t = threadIdx.x; t < total; t += kBlock * kAtOnce) {
-                // (Beyond the last word that one again.)
+                // (Beyond the last word that one is read, and not flushed again:
+                // hundreds of atomics on one word.)
                 uint32_t v[kAtOnce];
-                auto at = [&](int j) { return t + j * kBlock < total ? t + j * kBlock : total - 1; };
                 auto word = [&](int w) { return brick + ((w >> lgx) * Shape::kBXw + (w & ((1 << lgx) - 1))); };
 #pragma unroll
-                for (int j = 0; j < kAtOnce; ++j) v[j] = *word(at(j));
+                for (int j = 0; j < kAtOnce; ++j) v[j] = *word(t + j * kBlock < total ? t + j * kBlock : total - 1);
 #pragma unroll
                 for (int j = 0; j < kAtOnce; ++j) {
-                    if (v[j] == 0u) continue;
-                    const int w = at(j), r = w >> lgx;
+                    const int w = t + j * kBlock, r = w >> lgx;
+                    if (w >= total || v[j] == 0u) continue;
                     *word(w) = 0u;  // zero for the next item
                     __hip_atomic_fetch_or(dst + ((int64_t)(r >> LGY) * bg.dim[1] + (r & ((1 << LGY) - 1))) * row_words +
                                               (w & ((1 << lgx) - 1)),
