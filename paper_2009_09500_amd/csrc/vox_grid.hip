@@ -169,12 +169,14 @@ __device__ __forceinline__ bool slab_cut(const uint32_t* load, uint32_t runs, ui
 // workgroup 0, which sees all segments as the others do.
 //
 // Bound: latency (one launch, the segments from L2, a few divisions a hit).
-// Against the clear and one device atomic a voxel (25 G a second), cleared, us a
-// call: uniform end points, 1 000 segments in 256^3 7.2 / 11.5, 16 384 there
-// 37 / 85, 16 384 in 512^3 51 / 186; the same in one z slice 10.7 / 20.8,
-// 57 / 250 and 86 / 210 (without the cut 40, 615 and 1175, the work of one
-// workgroup; the estimate costs 0.3 of the 7.2); at most 8 voxels long,
-// 16 384 in 512^3 13.4 / 11.3, and in one slice 18.1 / 11.0 (without the cut 92).
+// Against the clear and device atomics on the volume (k_grid_direct), cleared, us a
+// call: uniform end points, 1 000 segments in 256^3 7.4 / 10.4, 16 384 there
+// 38 / 76, 16 384 in 512^3 50 / 164; the same in one z slice 10.8 / 20.8,
+// 57 / 161 and 85 / 159 (without the cut 40, 615 and 1175, the work of one
+// workgroup; the estimate costs 0.3 of the 7.4); at most 8 voxels long,
+// 16 384 in 512^3 13.4 / 11.1, and in one slice 18.1 / 10.2 (without the cut 92);
+// all in 8 rows of one slice there, one boundary's unit of words, 859 / 467, but
+// 4 000 of them 225 / 1540.
 // Windows by exact divisions, and by every lane for its own segment, hit or not:
 // 74 us for 16 384 uniform ones in 256^3.
 template <bool kAligned8, bool kEuclid>
@@ -450,13 +452,15 @@ static int64_t slab_words(int64_t nwords) {
 
 // Which calls take the slabs.  Every workgroup reads every segment, 0.3 us a
 // thousand and more (30 000 in 300 x 299 x 187, uniform / at most 8 voxels long:
-// 61 / 17 us, direct 158 / 12; 16 384 in 256^3 38 / 11, direct 85 / 11), so their
+// 60 / 17 us, direct 133 / 11; 16 384 in 256^3 38 / 11, direct 76 / 9), so their
 // product is bounded; more than
 // 512 runs (64 KiB each) lose against the direct form (1000 x 700 x 600, 4 000
-// short segments 33 against 28 us), and so do more than some segments in a small
-// volume, whose direct atomics are few and stay in the L2 (96^3, uniform ones:
-// 1 000 6.9 against 8.6 us, 2 000 10.3 / 8.4, 4 000 16.0 / 12.4; of log-uniform
-// length 6.5 / 8.3, 7.2 / 8.3, 8.3 / 8.5).
+// segments of log-uniform length 33 against 28 us), and so do many segments in a
+// small volume, whose direct atomics are few and stay in the L2 (us, slabs /
+// direct: 16 000 short ones in 96 x 86 x 87 11.9 / 8.9, 8 000 9.3 / 8.5; 16 000
+// uniform ones in 64^3 26.5 / 24.4, 8 000 16.3 / 16.0, but in 128^3 26 / 38).  The
+// line lies below where the two meet: 1 000 in 96^3 7.4 / 8.5, 2 000 7.6 / 8.4,
+// 4 000 11.1 / 11.9.
 constexpr int64_t kSlabMaxTests = int64_t(1) << 23;
 constexpr int64_t kSlabSmallVolume = 65536;  // words
 constexpr int64_t kSlabSmallSegments = 1536;
@@ -489,8 +493,8 @@ static hipError_t launch_slabs(const int32_t* segs, int64_t n, int32_t dx, int32
 // three to five launches and three passes cost 30 us with any segments at all
 // (1 000 segments in 256^3: 7 against 30 us a call).  With more it depends on
 // their lengths, which the host does not know: 16 384 of log-uniform length in
-// 512^3 / 960^3 take 20 / 77 us here and 38 / 122 on the brick path, but uniform
-// ones 48 / 312 and 42 / 133.
+// 512^3 / 960^3 take 19 / 77 us here and 38 / 123 on the brick path, but uniform
+// ones 50 / 308 and 42 / 136.
 constexpr int64_t kDirectMaxSegments = 16384;
 
 // The brick path serves calls with more segments than that, on volumes whose
