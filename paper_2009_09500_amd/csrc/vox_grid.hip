@@ -87,7 +87,13 @@ struct SlabBox {
     __device__ __forceinline__ void window(const AxisSteps& x, const AxisSteps& y, const AxisSteps& z, float n, int32_t dy,
                                            float& k0, float& k1) const {
         float a = 0.0f, b = n;
-        z.clip(zlo, zlo, a, b);
+        const bool slabs = whole && !(one && ylo == yhi);  // no more than z says
+        z.clip(zlo, slabs ? zhi : zlo, a, b);
+        if (slabs) {
+            k0 = a;
+            k1 = b;
+            return;
+        }
         y.clip(ylo, one ? yhi : dy - 1, a, b);
         if (one && ylo == yhi) x.clip(xlo, xhi, a, b);
         k0 = a <= b ? a : INFINITY;
@@ -126,7 +132,7 @@ __device__ __forceinline__ bool slab_cut(const uint32_t* load, uint32_t runs, ui
     }
     const uint32_t upto = wave_inclusive_sum_dpp(sum);
     const uint32_t all = __builtin_amdgcn_readlane(upto, kWave - 1);
-    if (__builtin_amdgcn_ballot_w64(slab_uneven(all, max, runs, n, samples)) == 0) return false;
+    if (__builtin_amdgcn_ballot_w64(slab_uneven(all, max, runs, n, samples, words)) == 0) return false;
     const uint32_t base = slab_base(all, runs), total = runs * base + all;
     for (uint32_t e = 0; e < 2u; ++e) {
         const uint32_t r = blockIdx.x + e;
@@ -164,25 +170,26 @@ __device__ __forceinline__ bool slab_cut(const uint32_t* load, uint32_t runs, ui
 // division per axis at its start, testing each voxel against the run.
 // The runs are the same number of words each, or cut by the work in them (slab_cut)
 // where the segments lie in few of them: the workgroups begin with the first while
-// one wave of each looks at the estimate, and begin again with the second.
+// the last wave of each makes an estimate, and begin again with the second.  (Without
+// `look` there is too little work for a cut.)
 // Counts: each group of 64 segments by one workgroup.  The status word: by
 // workgroup 0, which sees all segments as the others do.
 //
 // Bound: latency (one launch, the segments from L2, a few divisions a hit).
 // Against the clear and device atomics on the volume (k_grid_direct), cleared, us a
-// call: uniform end points, 1 000 segments in 256^3 7.4 / 10.4, 16 384 there
-// 38 / 76, 16 384 in 512^3 50 / 164; the same in one z slice 10.8 / 20.8,
-// 57 / 161 and 85 / 159 (without the cut 40, 615 and 1175, the work of one
-// workgroup; the estimate costs 0.3 of the 7.4); at most 8 voxels long,
-// 16 384 in 512^3 13.4 / 11.1, and in one slice 18.1 / 10.2 (without the cut 92);
-// all in 8 rows of one slice there, one boundary's unit of words, 859 / 467, but
-// 4 000 of them 225 / 1540.
+// call: uniform end points, 1 000 segments in 256^3 7.1 / 10.4, 16 384 there
+// 36 / 76, 16 384 in 512^3 47 / 164; the same in one z slice 14.2 / 20.8,
+// 58 / 161 and 85 / 159 (without the cut 40, 615 and 1175, the work of one
+// workgroup; the estimate costs 0.1 to 0.3 of the 7.1, and 0.6 where all waves wait
+// for it); at most 8 voxels long, 16 384 in 512^3 13.3 / 11.1, and in one slice
+// 18.4 / 10.2 (without the cut 92); all in 8 rows of one slice there, few units of
+// words, 864 / 467, but 4 000 of them 226 / 1540.
 // Windows by exact divisions, and by every lane for its own segment, hit or not:
 // 74 us for 16 384 uniform ones in 256^3.
 template <bool kAligned8, bool kEuclid>
 __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __restrict__ segs, int32_t n, int32_t dx,
                                                            int32_t dy, int32_t dz, uint32_t* __restrict__ grid,
-                                                           uint32_t nwords, uint32_t words, bool clear,
+                                                           uint32_t nwords, uint32_t words, bool clear, bool look,
                                                            int32_t* __restrict__ counts,
                                                            int32_t* __restrict__ status) {
     extern __shared__ __align__(16) uint32_t run[];
@@ -195,15 +202,25 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
         return ((uint32_t)g.p0[0] < (uint32_t)dx) & ((uint32_t)g.p1[0] < (uint32_t)dx) & ((uint32_t)g.p0[1] < (uint32_t)dy) &
                ((uint32_t)g.p1[1] < (uint32_t)dy) & ((uint32_t)g.p0[2] < (uint32_t)dz) & ((uint32_t)g.p1[2] < (uint32_t)dz);
     };
-    // The work in each of the runs of `words` words, by a sample a thread of the
-    // last waves (one a SIMD: all others wait for them): its own spread over the
-    // runs from one end point's to the other's.  (Eight neighbours at a time: whole
-    // lines.)
+    // The last wave looks at the work in each of the runs of `words` words, by
+    // samples, several a lane.  (Eight neighbours at a time: whole lines; beyond the
+    // last, that one again.)
     const uint32_t samples = (uint32_t)n < kSlabSamples ? (uint32_t)n : kSlabSamples;
-    const uint32_t st = threadIdx.x - (kSlabBlock - kSlabSamples);
-    Seg g = {};
-    if (st < samples)
-        g = load_seg<kAligned8>(segs, (uint32_t)n <= kSlabSamples ? st : st / 8u * (uint32_t)n / (kSlabSamples / 8u) + st % 8u);
+    const bool looks = look && wave == kSlabBlock / kWave - 1;
+    constexpr int kSamplesALane = kSlabSamples / kWave;
+    Seg sample[kSamplesALane];
+    if (looks) {
+#pragma unroll
+        for (int j = 0; j < kSamplesALane; ++j) {
+            const uint32_t st = (uint32_t)j * kWave + lane;
+            sample[j] = load_seg<kAligned8>(segs, (uint32_t)n > kSlabSamples ? st / 8u * (uint32_t)n / (kSlabSamples / 8u) + st % 8u
+                                                  : st < samples ? st : samples - 1u);
+        }
+    }
+    // Segments of a round: the last wave takes none where the others have two a lane
+    // at most.  (A few more than 1 000 segments in 256^3, one round of all waves: 7.8
+    // us, waiting for the wave that does both.)
+    const int32_t round = look && n <= 2 * (kSlabBlock - kWave) ? kSlabBlock - kWave : kSlabBlock;
     // The thread's first two segments (beyond the last, that one again).
     auto load_at = [&](int32_t i) {
         i += (int32_t)threadIdx.x;
@@ -212,10 +229,9 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
     Seg sa = {}, sb = {};
     if (n > 0) {
         sa = load_at(0);
-        sb = load_at(kSlabBlock);
+        sb = load_at(round);
     }
-    const Seg own = sa;
-    if (threadIdx.x < kSlabMaxRuns) load[threadIdx.x] = 0u;
+    const Seg own[2] = {sa, sb};
     if (threadIdx.x == 0) {
         bad_s = 0;
         cut_s = 0u;
@@ -248,7 +264,17 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
         take_run(first, nwords - first < words ? nwords : first + words);
     }
     lds_barrier();
-    if (st < samples) {
+    auto wave_fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // The others begin meanwhile, and leave off when the runs are cut anew.
+    if (looks) {
+#pragma unroll
+        for (uint32_t i = 0; i < kSlabMaxRuns / kWave; ++i) load[i * kWave + lane] = 0u;
+        wave_fence();
+        // A sample's work spread over the runs from one end point's to the other's.
         // (Out by one at most, and the same for every workgroup; a segment that is
         // not inside the volume counts for the runs nearest to it.)
         const float per = __builtin_amdgcn_rcpf((float)words * 32.0f), last = (float)(gridDim.x - 1u);
@@ -256,43 +282,46 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
             const float row = (float)(int32_t)((uint32_t)p[2] * (uint32_t)dy + (uint32_t)p[1]);
             return fminf(fmaxf((row * (float)dx + (float)p[0]) * per, 0.0f), last);
         };
-        const float r0 = place(g.p0), r1 = place(g.p1);
-        const uint32_t lo = (uint32_t)fminf(r0, r1), hi = (uint32_t)fmaxf(r0, r1);
-        uint32_t N = 0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const uint32_t d = (uint32_t)g.p1[a] - (uint32_t)g.p0[a];
-            const int32_t m = (int32_t)d < 0 ? (int32_t)(0u - d) : (int32_t)d;
-            N = (uint32_t)m > N ? (uint32_t)m : N;
+        for (int j = 0; j < kSamplesALane; ++j) {
+            const Seg& g = sample[j];
+            const float r0 = place(g.p0), r1 = place(g.p1);
+            const uint32_t lo = (uint32_t)fminf(r0, r1), hi = (uint32_t)fmaxf(r0, r1);
+            uint32_t N = 0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const uint32_t d = (uint32_t)g.p1[a] - (uint32_t)g.p0[a];
+                const int32_t m = (int32_t)d < 0 ? (int32_t)(0u - d) : (int32_t)d;
+                N = (uint32_t)m > N ? (uint32_t)m : N;
+            }
+            const uint32_t work = (uint32_t)j * kWave + lane < samples ? slab_work(N, hi - lo + 1u) : 0u;
+            atomicAdd(&load[lo], work);
+            if (hi + 1u < kSlabMaxRuns) atomicAdd(&load[hi + 1u], 0u - work);
         }
-        const uint32_t work = slab_work(N, hi - lo + 1u);
-        atomicAdd(&load[lo], work);
-        if (hi + 1u < kSlabMaxRuns) atomicAdd(&load[hi + 1u], 0u - work);
+        wave_fence();
+        if (slab_cut(load, gridDim.x, (uint32_t)n, samples, nwords, words, bounds_s) && lane == 0)
+            __hip_atomic_store(&cut_s, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    lds_barrier();
-    // One wave looks whether the runs are cut anew; the others begin, and leave
-    // off when they are.
-    if (wave == 0u && slab_cut(load, gridDim.x, (uint32_t)n, samples, nwords, words, bounds_s) && lane == 0)
-        __hip_atomic_store(&cut_s, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     auto cut_anew = [&] { return __hip_atomic_load(&cut_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u; };
 
-    auto wave_fence = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     bool first = true;  // the runs are not cut anew, or not yet
     // The voxels of the queue's segments [0, count), count <= 64.
     auto work = [&](uint32_t count) {
         uint32_t k0 = 0, len = 0;
         Seg g = {};
-        if (n <= kSlabBlock) {  // a lane of this wave has it
-            const int from = (int)(h.queue[lane] % kWave) << 2;
+        if (n <= 2 * round) {  // a lane of this wave has it
+            const int32_t i = (int32_t)h.queue[lane];
+            const int from = i % kWave << 2;
+            auto take = [&](const Seg& of, bool mine) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                g.p0[a] = __builtin_amdgcn_ds_bpermute(from, own.p0[a]);
-                g.p1[a] = __builtin_amdgcn_ds_bpermute(from, own.p1[a]);
-            }
+                for (int a = 0; a < 3; ++a) {
+                    const int32_t v0 = __builtin_amdgcn_ds_bpermute(from, of.p0[a]), v1 = __builtin_amdgcn_ds_bpermute(from, of.p1[a]);
+                    g.p0[a] = mine ? v0 : g.p0[a];
+                    g.p1[a] = mine ? v1 : g.p1[a];
+                }
+            };
+            take(own[0], true);
+            if (n > round) take(own[1], i >= round);
         } else if (lane < count) {
             g = load_seg<kAligned8>(segs, h.queue[lane]);
         }
@@ -395,14 +424,14 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
                 (uint32_t)i;
         queued += (uint32_t)__popcll(m);
     };
-    const int32_t wave0 = (int32_t)wave * kWave;
+    const int32_t wave0 = (int32_t)wave * kWave < round ? (int32_t)wave * kWave : n;
     for (;; first = false) {
         for (int32_t i0 = 0;;) {
-            for (; i0 + wave0 < n && queued < (uint32_t)kWave; i0 += 2 * kSlabBlock) {
+            for (; i0 + wave0 < n && queued < (uint32_t)kWave; i0 += 2 * round) {
                 test(sa, i0);
-                sa = load_at(i0 + 2 * kSlabBlock);
-                test(sb, i0 + kSlabBlock);
-                sb = load_at(i0 + 3 * kSlabBlock);
+                sa = load_at(i0 + 2 * round);
+                test(sb, i0 + round);
+                sb = load_at(i0 + 3 * round);
             }
             if (queued == 0 || (first && cut_anew())) break;
             wave_fence();
@@ -420,7 +449,7 @@ __global__ __launch_bounds__(kSlabBlock) void k_grid_slabs(const int32_t* __rest
         take_run(__builtin_amdgcn_readfirstlane(bounds_s[0]), __builtin_amdgcn_readfirstlane(bounds_s[1]));
         queued = 0;
         sa = load_at(0);
-        sb = load_at(kSlabBlock);
+        sb = load_at(round);
         lds_barrier();
     }
     if (blockIdx.x == 0 && __ballot(bad) != 0 && lane == 0) atomicOr(&bad_s, kStatusOutOfRange);
@@ -452,7 +481,7 @@ static int64_t slab_words(int64_t nwords) {
 
 // Which calls take the slabs.  Every workgroup reads every segment, 0.3 us a
 // thousand and more (30 000 in 300 x 299 x 187, uniform / at most 8 voxels long:
-// 60 / 17 us, direct 133 / 11; 16 384 in 256^3 38 / 11, direct 76 / 9), so their
+// 61 / 17 us, direct 133 / 11; 16 384 in 256^3 36 / 11, direct 76 / 9), so their
 // product is bounded; more than
 // 512 runs (64 KiB each) lose against the direct form (1000 x 700 x 600, 4 000
 // segments of log-uniform length 33 against 28 us), and so do many segments in a
@@ -484,8 +513,9 @@ static hipError_t launch_slabs(const int32_t* segs, int64_t n, int32_t dx, int32
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                                        (int)slab_room(kSlabMaxWords) * 4);
     if (attr != hipSuccess) return attr;
+    const int32_t side = dx > dy ? (dx > dz ? dx : dz) : (dy > dz ? dy : dz);
     k_grid_slabs<kAligned8, kEuclid><<<dim3(wgs), kSlabBlock, (size_t)slab_room((uint32_t)w) * 4, stream>>>(
-        segs, (int32_t)n, dx, dy, dz, grid, (uint32_t)nwords, (uint32_t)w, clear, counts, status);
+        segs, (int32_t)n, dx, dy, dz, grid, (uint32_t)nwords, (uint32_t)w, clear, slab_look(n, side, w), counts, status);
     return hipGetLastError();
 }
 
@@ -494,7 +524,7 @@ static hipError_t launch_slabs(const int32_t* segs, int64_t n, int32_t dx, int32
 // (1 000 segments in 256^3: 7 against 30 us a call).  With more it depends on
 // their lengths, which the host does not know: 16 384 of log-uniform length in
 // 512^3 / 960^3 take 19 / 77 us here and 38 / 123 on the brick path, but uniform
-// ones 50 / 308 and 42 / 136.
+// ones 47 / 308 and 42 / 136.
 constexpr int64_t kDirectMaxSegments = 16384;
 
 // The brick path serves calls with more segments than that, on volumes whose

@@ -37,20 +37,38 @@ __host__ __device__ __forceinline__ uint32_t slab_work(uint32_t N, uint32_t span
     return (uint32_t)((float)(N < (1u << 18) ? N : 1u << 18) * per) + 13u;
 }
 
+// Whether a cut by work pays where a run has `work` of n segments: the workgroup that
+// has it takes some 3 ns of each of its waves a voxel (a wave has 64 of the segments
+// at a time), of which a cut leaves at best what 32 words have, and beginning again
+// costs 6 us.  us a call, uncut / cut: in one slice of 256^3, 60 segments of 120
+// voxels 25.1 / 8.8, 1 000 of 5 voxels 8.8 / 13.2, 2 100 of them 14.8 / 12.8; in one
+// slice of 64^3 (runs of 64 words), 1 500 of 30 voxels 13.9 / 17.8.
+constexpr float kSlabLeastWork = 2048.0f;  // a wave
+__host__ __device__ __forceinline__ bool slab_pays(float work, uint32_t n, uint32_t words) {
+    const float waves = n < 16u * 64u ? (float)((n + 63u) / 64u) : 16.0f;
+    return work * (float)(words - 32u) > kSlabLeastWork * waves * (float)words;
+}
+
 // What every run weighs for its words alone, and whether the estimate (the runs'
 // work `load`, its sum and maximum, from `samples` of the n segments) asks for a
-// cut by work: a run with more than 16 times the mean, and more of it than
-// some microseconds.  (Uniform end points give 1.5 times the mean, a corner of a
-// quarter of the sides 6; cut at 6 such a corner took 4 000 segments in 256^3 from
-// 14.4 to 17.5 us, since cuts within a slice make every slice two workgroups'.)
+// cut by work: a run with more than 16 times the mean, and enough of it.  (Uniform end
+// points give 1.5 times the mean, a corner of a quarter of the sides 6; cut at 6 such
+// a corner took 4 000 segments in 256^3 from 14.4 to 17.5 us, since cuts within a
+// slice make every slice two workgroups'.)
 __host__ __device__ __forceinline__ uint32_t slab_base(uint32_t sum, uint32_t runs) {
     return 3u * ((sum + runs - 1u) / runs);
 }
 __host__ __device__ __forceinline__ bool slab_uneven(uint32_t sum, uint32_t max, uint32_t runs, uint32_t n,
-                                                     uint32_t samples) {
+                                                     uint32_t samples, uint32_t words) {
     // (The last: slab_base(sum, runs) >= kSlabMinBase.)
-    return ((float)max * (float)runs > 16.0f * (float)sum) & ((float)max * (float)n > 8192.0f * (float)samples) &
+    return ((float)max * (float)runs > 16.0f * (float)sum) & slab_pays((float)max * (float)n / (float)samples, n, words) &
            (sum > runs * ((kSlabMinBase + 2u) / 3u - 1u));
+}
+
+// Whether n segments inside a volume of this longest side can have as much work in
+// one run.
+inline bool slab_look(int64_t n, int32_t side, int64_t words) {
+    return slab_pays((float)n * (float)(side + 12), (uint32_t)n, (uint32_t)words);
 }
 
 // Weight before the r-th of `runs` boundaries, of all runs' weight `total`.

@@ -45,11 +45,13 @@ int main(int argc, char** argv) {
                 max = w > max ? w : max;
             }
             if (sum >> 32) ++bad;
-            if (!vox::slab_uneven((uint32_t)sum, max, runs, n, samples)) {
+            if (!vox::slab_uneven((uint32_t)sum, max, runs, n, samples, words)) {
                 ++even;
                 continue;
             }
             ++cuts;
+            // (Segments of less than `longest` steps.)
+            if (!vox::slab_look(n, (int32_t)longest, words)) ++bad;
             const uint32_t base = vox::slab_base((uint32_t)sum, runs) / (light ? 6u : 1u);
             if ((uint64_t)base * runs + sum >= 1ull << 32) ++bad;
             const uint32_t total = base * runs + (uint32_t)sum;
