@@ -51,3 +51,12 @@ def test_many_gathered_segments(n, kind):
     segs[n // 2, 0] = 300
     check(segs, dims, misaligned=True, out=2)
     check(segs, dims, clear=False, out=2)
+
+
+# Around one and two segments a lane of the waves that take any, and with too few
+# for an estimate; runs of whole slabs, of parts of one row, and of anything.
+@pytest.mark.parametrize("n", [7, 9, 960, 961, 1024, 1920, 1921, 2048, 2049])
+@pytest.mark.parametrize("dims", [(256, 256, 256), (2048, 1, 1056), (1 << 16, 3, 33), (301, 251, 199)])
+def test_segments_a_lane(dims, n):
+    check(gathered(dims, n, "slice", n), dims)
+    check(gathered(dims, n, "", n), dims, clear=False, counts=False, misaligned=True)
